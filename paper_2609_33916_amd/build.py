@@ -25,7 +25,7 @@ SOURCES = {
     "dkdv.hip": [],
     "bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
 }
-DEPENDS = ["attn.hip", "dkdv.hip", "bwd.hip", "launch.hpp", "kernels.hpp", "common.hpp"]
+DEPENDS = ["attn.hip", "dkdv.hip", "bwd.hip", "launch.hpp", "kernels.hpp", "common.hpp", "grid.hpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

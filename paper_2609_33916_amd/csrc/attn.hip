@@ -57,6 +57,11 @@ ScaleParts split_scale(float scale, int dtype) {
   return s;
 }
 
+// resident four-wave forward workgroups per compute unit, about
+template <typename T> constexpr int fwd_per_cu(int d) {
+  return std::is_same<T, bf16>::value ? (d == 128 ? 2 : 4) : (d == 128 ? 1 : d == 64 ? 2 : 3);
+}
+
 // bf16 at d = 128: the ping-pong forward (256 queries per eight-wave
 // workgroup); otherwise the four-wave forward (128 queries per workgroup).
 // At d <= 64 a tile's softmax arithmetic outlasts its products, so the
@@ -64,12 +69,10 @@ ScaleParts split_scale(float scale, int dtype) {
 template <typename T, int D, bool CAUSAL>
 void launch_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
   if constexpr (std::is_same<T, bf16>::value && D == 128) {
-    a.ntiles = (a.n + kFwdPpBQ - 1) / kFwdPpBQ;
-    a.nblocks = heads * a.ntiles;
+    attn::set_grid(a, heads, kFwdPpBQ, 1);
     hipLaunchKernelGGL((attn::fwd_pp_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(512), 0, st, a);
   } else {
-    a.ntiles = (a.n + kFwdBQ - 1) / kFwdBQ;
-    a.nblocks = heads * a.ntiles;
+    attn::set_grid(a, heads, kFwdBQ, fwd_per_cu<T>(D));
     hipLaunchKernelGGL((attn::fwd_kernel<T, D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
@@ -81,8 +84,7 @@ void launch_dkdv(attn::BwdArgs a, int heads, hipStream_t st) {
   if constexpr (std::is_same<T, bf16>::value) {
     attn::launch_dkdv16<D, CAUSAL, MAT, false>(a, heads, st);
   } else {
-    a.ntiles = (a.n + kDkvBKV - 1) / kDkvBKV;
-    a.nblocks = heads * a.ntiles;
+    attn::set_grid(a, heads, kDkvBKV, D == 128 ? 1 : 2);
     hipLaunchKernelGGL((attn::dkdv_kernel<T, D, CAUSAL, MAT>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
@@ -92,8 +94,7 @@ void launch_dq(attn::BwdArgs a, int heads, hipStream_t st) {
   if constexpr (std::is_same<T, bf16>::value) {
     attn::launch_dq16<D, CAUSAL, MAT>(a, heads, st);
   } else {
-    a.ntiles = (a.n + kFwdBQ - 1) / kFwdBQ;
-    a.nblocks = heads * a.ntiles;
+    attn::set_grid(a, heads, kFwdBQ, D == 128 ? 1 : 2);
     hipLaunchKernelGGL((attn::dq_kernel<T, D, CAUSAL, MAT>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
@@ -105,8 +106,7 @@ template <typename T, int D, bool CAUSAL>
 void launch_dkdv_aq(attn::BwdArgs a, int heads, hipStream_t st) {
   if constexpr (std::is_same<T, bf16>::value) {
     constexpr int nw = attn::dkdv16_nw(D, false, true), bkv = attn::dkdv16_bkv(D, false, true);
-    a.ntiles = (a.n + bkv - 1) / bkv;
-    a.nblocks = heads * a.ntiles;
+    attn::set_grid(a, heads, bkv, D == 128 ? 1 : 2);
     hipLaunchKernelGGL((attn::dkdv16_kernel<D, CAUSAL, nw, attn::kDkv16BQ, false, true, 1>), dim3(a.nblocks),
                        dim3(64 * nw), 0, st, a);
   }
@@ -114,8 +114,7 @@ void launch_dkdv_aq(attn::BwdArgs a, int heads, hipStream_t st) {
 
 template <typename T, int D, bool CAUSAL>
 void launch_mat_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
-  a.ntiles = (a.n + kFwdBQ - 1) / kFwdBQ;
-  a.nblocks = heads * a.ntiles;
+  attn::set_grid(a, heads, kFwdBQ, fwd_per_cu<T>(D));
   hipLaunchKernelGGL((attn::mat_fwd_kernel<T, D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
 }
 

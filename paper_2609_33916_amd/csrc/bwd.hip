@@ -8,8 +8,7 @@ namespace attn {
 
 template <int D, bool CAUSAL, bool MAT>
 void launch_dq16(BwdArgs a, int heads, hipStream_t st) {
-  a.ntiles = (a.n + kDqBQ - 1) / kDqBQ;
-  a.nblocks = heads * a.ntiles;
+  set_grid(a, heads, kDqBQ, D == 128 ? 2 : D == 64 ? 3 : 4);
   hipLaunchKernelGGL((dq_kernel<bf16, D, CAUSAL, MAT>), dim3(a.nblocks), dim3(256), 0, st, a);
 }
 

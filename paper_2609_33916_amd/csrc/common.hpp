@@ -1,6 +1,6 @@
 // Device building blocks for the gfx950 attention kernels: element traits,
 // matrix-core (MFMA) wrappers, LDS tile layout and operand reads, lane-half
-// reductions and the workgroup -> (head, tile) schedule.
+// reductions (the workgroup -> (head, tile) schedule is in grid.hpp).
 //
 // MFMA 32x32 register layouts (wave64, lane l, half h = l / 32, c = l % 32):
 //   A operand   : row c, k slots [h*KP, h*KP + KP)
@@ -35,6 +35,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include "grid.hpp"
 
 namespace attn {
 
@@ -697,22 +699,6 @@ template <typename T>
 __device__ __forceinline__ void store_run16(T* p, const u32x4 (&r)[Run16<T>::NC]) {
 #pragma unroll
   for (int e = 0; e < Run16<T>::NC; ++e) *(u32x4*)(p + e * Elem<T>::CH) = r[e];
-}
-
-// --------------------------------------------------------- scheduling --
-// Workgroup id -> (head, tile). Consecutive workgroup ids are dispatched
-// round-robin over the 8 XCDs (each with its own L2); remapping gives every
-// XCD a contiguous range of (head, tile) so the tiles of one head, which
-// share K and V, run on the same L2. With `reverse`, tiles of a head are
-// issued from the last (most work under a causal mask) to the first.
-__device__ __forceinline__ void block_map(int bid, int nblocks, int ntiles, bool reverse,
-                                          int& head, int& tile) {
-  const int per = nblocks >> 3;
-  int lin = bid;
-  if (bid < per * 8) lin = (bid & 7) * per + (bid >> 3);
-  head = lin / ntiles;
-  const int t = lin - head * ntiles;
-  tile = reverse ? ntiles - 1 - t : t;
 }
 
 }  // namespace attn

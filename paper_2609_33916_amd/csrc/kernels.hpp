@@ -40,6 +40,7 @@ struct FwdArgs {
   int n;
   int ntiles;    // query tiles per head
   int nblocks;   // grid size
+  int hgroup;    // causal: heads issued together (block_map)
   float sl2;     // |scale| * log2(e), clamped away from 0
   uint32_t qflip;  // sign-bit mask applied to Q (negative scale)
   void* amat;      // materialising forward only: the attention matrix P
@@ -60,6 +61,7 @@ struct BwdArgs {
   int n;
   int ntiles;
   int nblocks;
+  int hgroup;    // causal: heads issued together (block_map)
   float sl2;
   float dk_scale;  // scale (dK = s dS^T Q; K is read sign-flipped when scale < 0)
   float dq_scale;  // scale
@@ -143,7 +145,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) fwd_kernel(const 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, qt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL, head, qt);
+  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, CAUSAL, head, qt);
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
@@ -381,7 +383,7 @@ __global__ void __launch_bounds__(512) fwd_pp_kernel(const FwdArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = w >> 2, wi = w & 3;
   int head, qt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL, head, qt);
+  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, CAUSAL, head, qt);
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
@@ -590,7 +592,7 @@ __global__ void __launch_bounds__(256) mat_fwd_kernel(const FwdArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, qt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL, head, qt);
+  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, CAUSAL, head, qt);
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
@@ -790,7 +792,7 @@ __global__ void __launch_bounds__(256) dkdv_kernel(const BwdArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, kt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, false, head, kt);
+  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, false, head, kt);
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
@@ -971,7 +973,7 @@ __global__ void __launch_bounds__(64 * NW, 2) dkdv16_kernel(const BwdArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, kt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, false, head, kt);
+  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, false, head, kt);
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const bf16* Qg = (const bf16*)a.q + hoff;
@@ -1411,7 +1413,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) dq_kernel(const B
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, qt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL, head, qt);
+  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, CAUSAL, head, qt);
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
