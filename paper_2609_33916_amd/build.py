@@ -23,9 +23,10 @@ LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 SOURCES = {
     "attn.hip": [],
     "dkdv.hip": [],
+    "split.hip": [],
     "bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
 }
-DEPENDS = ["attn.hip", "dkdv.hip", "bwd.hip", "launch.hpp", "kernels.hpp", "common.hpp", "grid.hpp"]
+DEPENDS = ["attn.hip", "dkdv.hip", "bwd.hip", "split.hip", "launch.hpp", "kernels.hpp", "split.hpp", "common.hpp", "grid.hpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

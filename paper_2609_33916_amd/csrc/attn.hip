@@ -68,6 +68,10 @@ template <typename T> constexpr int fwd_per_cu(int d) {
 // ping-pong phases would wait on the softmax.
 template <typename T, int D, bool CAUSAL>
 void launch_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
+  if (attn::use_split(attn::kFwd, std::is_same<T, bf16>::value, D, CAUSAL, heads, a.n)) {
+    attn::launch_fwd_split<T, D, CAUSAL>(a, heads, st);
+    return;
+  }
   if constexpr (std::is_same<T, bf16>::value && D == 128) {
     attn::set_grid(a, heads, kFwdPpBQ, 1);
     hipLaunchKernelGGL((attn::fwd_pp_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(512), 0, st, a);
@@ -81,6 +85,12 @@ void launch_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
 // uses the 32-key-per-wave dK/dV kernel and the dQ kernel instantiated here.
 template <typename T, int D, bool CAUSAL, bool MAT = false>
 void launch_dkdv(attn::BwdArgs a, int heads, hipStream_t st) {
+  if constexpr (!MAT) {
+    if (attn::use_split(attn::kDkdv, std::is_same<T, bf16>::value, D, CAUSAL, heads, a.n)) {
+      attn::launch_dkdv_split<T, D, CAUSAL, false>(a, heads, st);
+      return;
+    }
+  }
   if constexpr (std::is_same<T, bf16>::value) {
     attn::launch_dkdv16<D, CAUSAL, MAT, false>(a, heads, st);
   } else {
@@ -91,6 +101,12 @@ void launch_dkdv(attn::BwdArgs a, int heads, hipStream_t st) {
 
 template <typename T, int D, bool CAUSAL, bool MAT = false>
 void launch_dq(attn::BwdArgs a, int heads, hipStream_t st) {
+  if constexpr (!MAT) {
+    if (attn::use_split(attn::kDq, std::is_same<T, bf16>::value, D, CAUSAL, heads, a.n)) {
+      attn::launch_dq_split<T, D, CAUSAL>(a, heads, st);
+      return;
+    }
+  }
   if constexpr (std::is_same<T, bf16>::value) {
     attn::launch_dq16<D, CAUSAL, MAT>(a, heads, st);
   } else {
@@ -105,6 +121,10 @@ void launch_dq(attn::BwdArgs a, int heads, hipStream_t st) {
 template <typename T, int D, bool CAUSAL>
 void launch_dkdv_aq(attn::BwdArgs a, int heads, hipStream_t st) {
   if constexpr (std::is_same<T, bf16>::value) {
+    if (attn::use_split(attn::kDkdv, true, D, CAUSAL, heads, a.n)) {   // as the fused path: the same dK and dV
+      attn::launch_dkdv_split<T, D, CAUSAL, true>(a, heads, st);
+      return;
+    }
     constexpr int nw = attn::dkdv16_nw(D, false, true), bkv = attn::dkdv16_bkv(D, false, true);
     attn::set_grid(a, heads, bkv, D == 128 ? 1 : 2);
     hipLaunchKernelGGL((attn::dkdv16_kernel<D, CAUSAL, nw, attn::kDkv16BQ, false, true, 1>), dim3(a.nblocks),

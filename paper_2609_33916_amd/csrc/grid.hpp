@@ -62,6 +62,35 @@ ATTN_HD int head_group(int heads, int ntiles, int per_cu) {
   return g < heads ? g : heads;
 }
 
+// The largest call, in 128-row tiles over all heads, that the kernels for small
+// grids (split.hpp) take: up to there they are faster, their quarter-length
+// chains of steps outweighing that each key tile serves 32 queries instead of
+// 128 or 256. Under the causal mask that holds for about twice the tiles, half
+// of them being short. Time of the large-grid kernels over theirs, measured
+// at n = 512 / 2048 / 8192:
+//   bf16, d = 128, forward  64 tiles 2.05 / 2.07 / 2.01, 128 tiles 1.38 / 1.18 / 1.10, 192 tiles 1.06 / 0.87 / 0.78
+//   the same causal         64 tiles 2.15 / 2.13 / 2.18, 256 tiles 1.11 / 1.11 / 1.05, 384 tiles 0.87 / 0.84 / 0.77
+//   bf16, d = 64, dK/dV     64 tiles 2.12 / 2.92 / 3.38, 256 tiles 1.04 / 1.18 / 1.23, 512 tiles 0.83 / 0.81 / 0.81
+//   f32, d = 64, dQ         64 tiles 2.78 / 3.08 / 3.23, 128 tiles 1.35 / 1.45 / 1.53, 256 tiles 0.80 / 0.79 / 0.79
+// With n below 512 a causal head has too few short tiles for the causal limit
+// (250 heads, n = 100, bf16, d = 64: 0.91), and at n <= 128 a bf16 backward at
+// d = 128 has at most four steps to share (n = 33 to 100, dK/dV: 0.81-0.92).
+enum Kind { kFwd, kDkdv, kDq };
+constexpr int split_limit(Kind kind, bool b16, int d, bool causal) {
+  constexpr int limit[2][3][3][2] = {   // [bf16][kind][d = 32, 64, 128][causal]
+      {{{160, 320}, {128, 320}, {128, 256}},
+       {{192, 384}, {192, 320}, {192, 256}},
+       {{192, 384}, {128, 320}, {192, 320}}},
+      {{{192, 384}, {128, 192}, {128, 256}},
+       {{192, 320}, {256, 384}, {112, 160}},
+       {{384, 384}, {192, 224}, {128, 192}}}};
+  return limit[b16][kind][d == 32 ? 0 : d == 64 ? 1 : 2][causal];
+}
+inline bool use_split(Kind kind, bool b16, int d, bool causal, int heads, int n) {
+  if (b16 && d == 128 && kind != kFwd && n <= 128) return false;
+  return (long long)heads * ((n + 127) / 128) <= split_limit(kind, b16, d, causal && n >= 512);
+}
+
 // Tiles per head, grid size and issue order of `heads` heads in tiles of
 // `rows` rows (Args: FwdArgs or BwdArgs).
 template <typename Args> inline void set_grid(Args& a, int heads, int rows, int per_cu) {

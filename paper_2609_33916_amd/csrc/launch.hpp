@@ -1,8 +1,8 @@
-// Launchers of the bfloat16 backward kernels, each in a translation unit of
-// its own (the build script gives each source its flags): dK/dV on
-// 16x16x32 MFMA in dkdv.hip (default machine scheduler), dQ in bwd.hip
-// (iterative-ILP scheduler); the forward kernels, in attn.hip, keep the
-// default scheduler.
+// Launchers that live in translation units of their own (the build script
+// gives each source its flags): bf16 dK/dV on 16x16x32 MFMA in dkdv.hip
+// (default machine scheduler), bf16 dQ in bwd.hip (iterative-ILP scheduler)
+// and the kernels for small grids in split.hip; the other kernels are
+// launched from attn.hip, with the default scheduler.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -41,5 +41,11 @@ void launch_dkdv16(BwdArgs a, int heads, hipStream_t st);
 
 template <int D, bool CAUSAL, bool MAT>
 void launch_dq16(BwdArgs a, int heads, hipStream_t st);
+
+// The kernels for small grids (split.hip): 32 rows per workgroup.
+constexpr int kSplitRows = 32;
+template <typename T, int D, bool CAUSAL> void launch_fwd_split(FwdArgs a, int heads, hipStream_t st);
+template <typename T, int D, bool CAUSAL, bool AQ> void launch_dkdv_split(BwdArgs a, int heads, hipStream_t st);
+template <typename T, int D, bool CAUSAL> void launch_dq_split(BwdArgs a, int heads, hipStream_t st);
 
 }  // namespace attn

@@ -1,0 +1,39 @@
+"""The kernels for small grids and their neighbours (GPU): grids just below and
+above the limit at which a call moves to the large-grid kernels, and lengths
+at the edges of their 32-row blocks and of the four waves' shares (1 to 9
+blocks), every output against float64 at the dtype's bound."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from helpers import OUTPUTS, TOL, compare, gpu_available, run_fwd_bwd, to_gpu, to_host64
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_block_and_wave_edges(dtype, d, causal):
+    for n in (31, 32, 33, 96, 128, 160, 257, 288):
+        w = workloads.Workload(f"split_n{n}", 1, 2, n, d, dtype, causal, 1.0, 1.0, 1.0, 100 + n + d)
+        inp = workloads.generate(w)
+        got = run_fwd_bwd(to_gpu(inp), -0.3 if n == 160 else w.scale, causal)
+        ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, -0.3 if n == 160 else w.scale, causal)
+        errs = compare({k: to_host64(got[k]) for k in OUTPUTS}, ref)
+        assert all(v <= TOL[dtype] for v in errs.values()), (n, errs)
+
+
+@pytest.mark.parametrize("heads", [28, 29, 48, 64, 65, 96, 97])
+def test_both_sides_of_the_limits(heads):
+    """512 rows are four 128-row tiles a head: limits of 112 to 384 tiles."""
+    for dtype, d, causal in (("bf16", 128, True), ("bf16", 64, False), ("f32", 64, True)):
+        w = workloads.Workload("limit", 1, heads, 512, d, dtype, causal, 1.0, 1.0, 1.0, heads)
+        inp = workloads.generate(w)
+        got = run_fwd_bwd(to_gpu(inp), w.scale, causal)
+        some = [(0, 0), (0, heads // 2), (0, heads - 1)]
+        ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, causal, heads=some)
+        host = {k: np.stack([to_host64(got[k])[b, h] for b, h in some]) for k in OUTPUTS}
+        errs = compare(host, ref)
+        assert all(v <= TOL[dtype] for v in errs.values()), (dtype, d, causal, errs)
