@@ -24,9 +24,10 @@ SOURCES = {
     "attn.hip": [],
     "dkdv.hip": [],
     "split.hip": [],
+    "f32x3.hip": [],
     "bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
 }
-DEPENDS = ["attn.hip", "dkdv.hip", "bwd.hip", "split.hip", "launch.hpp", "kernels.hpp", "split.hpp", "common.hpp", "grid.hpp"]
+DEPENDS = ["attn.hip", "dkdv.hip", "bwd.hip", "split.hip", "launch.hpp", "kernels.hpp", "split.hpp", "f32x3.hip", "f32x3.hpp", "common.hpp", "grid.hpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -22,7 +22,7 @@ using attn::bf16;
 
 constexpr int kFwdBQ = attn::kDqBQ;  // queries per forward / dQ workgroup
 constexpr int kFwdPpBQ = 256;        // queries per ping-pong forward workgroup
-constexpr int kDkvBKV = 128;  // keys per float32 dK/dV workgroup
+constexpr int kDkvBKV = 128;         // keys per float32 materialising dK/dV workgroup
 
 bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
@@ -62,27 +62,28 @@ template <typename T> constexpr int fwd_per_cu(int d) {
   return std::is_same<T, bf16>::value ? (d == 128 ? 2 : 4) : (d == 128 ? 1 : d == 64 ? 2 : 3);
 }
 
-// bf16 at d = 128: the ping-pong forward (256 queries per eight-wave
-// workgroup); otherwise the four-wave forward (128 queries per workgroup).
-// At d <= 64 a tile's softmax arithmetic outlasts its products, so the
-// ping-pong phases would wait on the softmax.
+// Small grids take the kernels of split.hpp. Otherwise, bf16 at d = 128: the
+// ping-pong forward (256 queries per eight-wave workgroup), and at d <= 64,
+// where a tile's softmax arithmetic outlasts its products, so that the
+// ping-pong phases would wait on the softmax, the four-wave forward (128
+// queries per workgroup); float32: f32x3.hpp.
 template <typename T, int D, bool CAUSAL>
 void launch_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
   if (attn::use_split(attn::kFwd, std::is_same<T, bf16>::value, D, CAUSAL, heads, a.n)) {
     attn::launch_fwd_split<T, D, CAUSAL>(a, heads, st);
-    return;
-  }
-  if constexpr (std::is_same<T, bf16>::value && D == 128) {
+  } else if constexpr (!std::is_same<T, bf16>::value) {
+    attn::launch_fwd_x3<D, CAUSAL>(a, heads, st);
+  } else if constexpr (D == 128) {
     attn::set_grid(a, heads, kFwdPpBQ, 1);
     hipLaunchKernelGGL((attn::fwd_pp_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(512), 0, st, a);
   } else {
     attn::set_grid(a, heads, kFwdBQ, fwd_per_cu<T>(D));
-    hipLaunchKernelGGL((attn::fwd_kernel<T, D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attn::fwd_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
 
-// bf16 dK/dV and dQ launch from dkdv.hip and bwd.hip (launch.hpp); float32
-// uses the 32-key-per-wave dK/dV kernel and the dQ kernel instantiated here.
+// bf16 dK/dV and dQ launch from dkdv.hip and bwd.hip (launch.hpp); the float32
+// materialising kernels are instantiated here.
 template <typename T, int D, bool CAUSAL, bool MAT = false>
 void launch_dkdv(attn::BwdArgs a, int heads, hipStream_t st) {
   if constexpr (!MAT) {
@@ -93,9 +94,11 @@ void launch_dkdv(attn::BwdArgs a, int heads, hipStream_t st) {
   }
   if constexpr (std::is_same<T, bf16>::value) {
     attn::launch_dkdv16<D, CAUSAL, MAT, false>(a, heads, st);
+  } else if constexpr (!MAT) {
+    attn::launch_dkdv_x3<D, CAUSAL>(a, heads, st);
   } else {
     attn::set_grid(a, heads, kDkvBKV, D == 128 ? 1 : 2);
-    hipLaunchKernelGGL((attn::dkdv_kernel<T, D, CAUSAL, MAT>), dim3(a.nblocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attn::mat_dkdv_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
 
@@ -109,9 +112,11 @@ void launch_dq(attn::BwdArgs a, int heads, hipStream_t st) {
   }
   if constexpr (std::is_same<T, bf16>::value) {
     attn::launch_dq16<D, CAUSAL, MAT>(a, heads, st);
+  } else if constexpr (!MAT) {
+    attn::launch_dq_x3<D, CAUSAL>(a, heads, st);
   } else {
     attn::set_grid(a, heads, kFwdBQ, D == 128 ? 1 : 2);
-    hipLaunchKernelGGL((attn::dq_kernel<T, D, CAUSAL, MAT>), dim3(a.nblocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attn::dq_kernel<float, D, CAUSAL, true>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
 

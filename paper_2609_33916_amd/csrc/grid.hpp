@@ -71,16 +71,17 @@ ATTN_HD int head_group(int heads, int ntiles, int per_cu) {
 //   bf16, d = 128, forward  64 tiles 2.05 / 2.07 / 2.01, 128 tiles 1.38 / 1.18 / 1.10, 192 tiles 1.06 / 0.87 / 0.78
 //   the same causal         64 tiles 2.15 / 2.13 / 2.18, 256 tiles 1.11 / 1.11 / 1.05, 384 tiles 0.87 / 0.84 / 0.77
 //   bf16, d = 64, dK/dV     64 tiles 2.12 / 2.92 / 3.38, 256 tiles 1.04 / 1.18 / 1.23, 512 tiles 0.83 / 0.81 / 0.81
-//   f32, d = 64, dQ         64 tiles 2.78 / 3.08 / 3.23, 128 tiles 1.35 / 1.45 / 1.53, 256 tiles 0.80 / 0.79 / 0.79
+//   f32, d = 64, dQ         64 tiles 1.54 / 1.65 / 1.68,  96 tiles 0.80 / 0.78,        256 tiles 0.51 / 0.48 / 0.46
+//   the same causal         64 tiles 1.57 / 1.69 / 1.71, 128 tiles 0.99 / 0.98 / 1.00, 256 tiles 0.69 / 0.68 / 0.68
 // With n below 512 a causal head has too few short tiles for the causal limit
 // (250 heads, n = 100, bf16, d = 64: 0.91), and at n <= 128 a bf16 backward at
 // d = 128 has at most four steps to share (n = 33 to 100, dK/dV: 0.81-0.92).
 enum Kind { kFwd, kDkdv, kDq };
 constexpr int split_limit(Kind kind, bool b16, int d, bool causal) {
   constexpr int limit[2][3][3][2] = {   // [bf16][kind][d = 32, 64, 128][causal]
-      {{{160, 320}, {128, 320}, {128, 256}},
-       {{192, 384}, {192, 320}, {192, 256}},
-       {{192, 384}, {128, 320}, {192, 320}}},
+      {{{128, 176}, {80, 128}, {128, 256}},
+       {{80, 176}, {80, 192}, {80, 160}},
+       {{80, 144}, {80, 112}, {128, 208}}},
       {{{192, 384}, {128, 192}, {128, 256}},
        {{192, 320}, {256, 384}, {112, 160}},
        {{384, 384}, {192, 224}, {128, 192}}}};
@@ -89,6 +90,22 @@ constexpr int split_limit(Kind kind, bool b16, int d, bool causal) {
 inline bool use_split(Kind kind, bool b16, int d, bool causal, int heads, int n) {
   if (b16 && d == 128 && kind != kFwd && n <= 128) return false;
   return (long long)heads * ((n + 127) / 128) <= split_limit(kind, b16, d, causal && n >= 512);
+}
+
+// The float32 kernels of f32x3.hpp come with four waves, or (d <= 64) with
+// eight that share every tile. Eight keep two waves on each SIMD while there
+// is one workgroup per compute unit; with more, two workgroups of four are
+// better, their barriers being independent. Time of eight over four at n = 512
+// / 2048, d = 64: 256 tiles forward 0.94 / 0.89, dK/dV 0.84 / 0.80, dQ 0.92 /
+// 0.88; 320 tiles 1.14 / 1.08, 1.13 / 1.10, 1.16 / 1.10; causal 384 tiles 1.01 /
+// 0.83, 0.84 / 0.72, 0.98 / 0.79, 512 tiles 1.09 / 0.89, 0.95 / 0.79, 1.07 /
+// 0.85. The d = 32 forward, whose tiles cost it more to split than to use, is
+// faster with eight at every size (64 heads, n = 2048: 211 against 216 us) but
+// those of n <= 64, which leave the second four nothing.
+inline bool x3_eight_waves(Kind kind, int d, bool causal, int heads, int n) {
+  if (d == 128 || n <= 64) return false;
+  if (d == 32 && kind == kFwd) return true;
+  return (long long)heads * ((n + 127) / 128) <= (causal && n >= 512 ? 384 : 256);
 }
 
 // Tiles per head, grid size and issue order of `heads` heads in tiles of

@@ -1,10 +1,15 @@
-// The three kernels of the fused attention forward+backward pass on gfx950.
+// The kernels of the fused attention forward+backward pass on gfx950, for
+// bfloat16 calls that fill the chip:
 //
-//   fwd_kernel  (query-owner)  O, L and the backward's row vector D
-//   dkdv_kernel (key-owner)    dK, dV; each workgroup owns a block of keys
+//   fwd_kernel, fwd_pp_kernel  (query-owner)  O, L and the backward's row
+//                              vector D
+//   dkdv16_kernel (key-owner)  dK, dV; each workgroup owns a block of keys
 //                              and sweeps the query tiles that see them
-//   dq_kernel   (query-owner)  dQ; each workgroup owns a block of queries
+//   dq_kernel     (query-owner)  dQ; each workgroup owns a block of queries
 //                              and sweeps the key tiles they see
+//
+// and the materialising path, the decode step and the atomic-dQ support. Small
+// grids take split.hpp, float32 calls f32x3.hpp.
 //
 // The scores S and probabilities P of a tile live only in registers: they
 // are produced by one MFMA product and consumed as the operand of the next
@@ -119,13 +124,14 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(const PrepArgs a) {
 }
 
 // ======================================================================
-// Forward: a workgroup owns BQ = 128 queries (32 per wave); K and V tiles of
+// Forward (bf16, d <= 64): a workgroup owns BQ = 128 queries (32 per wave); K and V tiles of
 // BKV = 64 keys are staged in LDS (double-buffered through registers).
 // Per wave and key tile:  S^T = K Q^T (rows = keys, cols = the wave's 32
 // queries), online softmax per column, O^T += V^T P^T.
 // ======================================================================
-template <typename T, int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) fwd_kernel(const FwdArgs a) {
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdArgs a) {
+  using T = bf16;
   using E = Elem<T>;
   using Frag = typename E::frag;
   constexpr int BQ = 128, BKV = 64, NKB = BKV / 32, NDB = D / 32;
@@ -133,9 +139,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) fwd_kernel(const 
   constexpr int KP = E::KP;
   constexpr int TD = D / (2 * KP);   // k-steps over d
   constexpr int T32 = 16 / KP;       // k-steps over a 32-row block
-  // bf16 at d = 128: padded K/V tiles (Pad32)
-  static constexpr bool P32 = sizeof(T) == 2 && D == 128;
-  using TL = Tile<T, BKV, D, P32>;
+  using TL = Tile<T, BKV, D>;
   // two stages of (K, V) in distinct LDS objects: the loop is unrolled by
   // two so every access names its stage statically, which lets the compiler
   // see that reads of one stage never wait on the copy into the other
@@ -159,11 +163,9 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) fwd_kernel(const 
   const int kv_end = CAUSAL ? min(n, q0 + BQ) : n;
   const int nt = (kv_end + BKV - 1) / BKV;
 
-  TileLoader<T, BKV, D, P32> kld(w, lane), vld(w, lane);
+  TileLoader<T, BKV, D> kld(w, lane), vld(w, lane);
   kld.issue(stA[0], Kg, 0, n, w);
   vld.issue(stA[1], Vg, 0, n, w);
-  kld.commit(stA[0]);
-  vld.commit(stA[1]);
   __syncthreads();
 
   f32x16 oacc[NDB];
@@ -187,17 +189,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) fwd_kernel(const 
       for (int b = 0; b < NKB; ++b) {
         s[b] = zero16();
 #pragma unroll
-        for (int t = 0; t < TD; ++t) mma(s[b], RowRead<T, D, P32>::get(kl, b, t, h, c), qf.f[t]);
-      }
-      // bf16 at d = 128: K row reads six products ahead of the score products
-      // (measured 1.5-2 % faster forward at n = 16384 than the compiler's two)
-      if constexpr (sizeof(T) == 2 && D == 128) {
-        ATTN_SCHED(kSchedDSRead, 6);
-#pragma unroll
-        for (int i = 0; i < NKB * TD; ++i) {
-          ATTN_SCHED(kSchedMFMA, 1);
-          ATTN_SCHED(kSchedDSRead, 1);
-        }
+        for (int t = 0; t < TD; ++t) mma(s[b], RowRead<T, D>::get(kl, b, t, h, c), qf.f[t]);
       }
       // lane (h, c): s[b][j] = raw score of key kv0 + 32b + 16h + j, query qi
       const bool edge = (kv0 + BKV > n) || (CAUSAL && kv0 + BKV - 1 > qw0);
@@ -250,13 +242,9 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) fwd_kernel(const 
           const Frag pf = FragFromAcc<T>::get(s[b], t);
 #pragma unroll
           for (int db = 0; db < NDB; ++db)
-            mma(oacc[db], TransRead<T, D, 64, P32>::get(vl, b, db, t, h, c), pf);
+            mma(oacc[db], TransRead<T, D>::get(vl, b, db, t, h, c), pf);
         }
       __builtin_amdgcn_s_setprio(0);
-    }
-    if (it + 1 < nt) {
-      kld.commit(nxt[0]);
-      vld.commit(nxt[1]);
     }
     __syncthreads();
   };
@@ -764,17 +752,16 @@ __global__ void __launch_bounds__(256) mat_fwd_kernel(const FwdArgs a) {
 }
 
 // ======================================================================
-// dK, dV: a workgroup owns BKV = 128 keys (32 per wave, held in registers as
-// B operands); Q and dO tiles of BQ = 64 queries are staged in LDS with
-// their base-2 log-sum-exp and D rows.
-// Per wave and 32-query block:  S = Q K^T, dP = dO V^T  (rows = queries,
-// cols = the wave's keys), P = 2^(S sl2 - L), dS = P (dP - D),
-// dV^T += dO^T P, dK^T += Q^T dS.
-// With MAT (materialising backward) S is not recomputed: each lane reads its
-// column of P (16 query rows) straight from the stored matrix.
+// dK, dV of the materialising path in float32: a workgroup owns BKV = 128 keys
+// (32 per wave, V held in registers as B operand); Q and dO tiles of BQ = 64
+// queries are staged in LDS with their D rows.
+// Per wave and 32-query block:  dP = dO V^T  (rows = queries, cols = the
+// wave's keys), dS = P (dP - D), dV^T += dO^T P, dK^T += Q^T dS, each lane
+// reading its column of P (16 query rows) straight from the stored matrix.
 // ======================================================================
-template <typename T, int D, bool CAUSAL, bool MAT = false>
-__global__ void __launch_bounds__(256) dkdv_kernel(const BwdArgs a) {
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256) mat_dkdv_kernel(const BwdArgs a) {
+  using T = float;
   using E = Elem<T>;
   using Frag = typename E::frag;
   constexpr int BKV = 128, BQ = 64, NQB = BQ / 32, NDB = D / 32;
@@ -782,12 +769,12 @@ __global__ void __launch_bounds__(256) dkdv_kernel(const BwdArgs a) {
   constexpr int KP = E::KP;
   constexpr int T32 = 16 / KP;
   using TL = Tile<T, BQ, D>;
-  // two stages of (Q, dO) with their L and D rows, in distinct LDS objects
+  // two stages of (Q, dO) with their D rows, in distinct LDS objects
   // (loop unrolled by two, as in the forward)
   __shared__ __attribute__((aligned(16))) T stA[2][TL::ELEMS];
   __shared__ __attribute__((aligned(16))) T stB[2][TL::ELEMS];
-  __shared__ __attribute__((aligned(16))) float ldA[2][BQ];
-  __shared__ __attribute__((aligned(16))) float ldB[2][BQ];
+  __shared__ __attribute__((aligned(16))) float ldA[BQ];
+  __shared__ __attribute__((aligned(16))) float ldB[BQ];
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -796,33 +783,25 @@ __global__ void __launch_bounds__(256) dkdv_kernel(const BwdArgs a) {
   const int n = a.n;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
-  const T* Kg = (const T*)a.k + hoff;
   const T* Vg = (const T*)a.v + hoff;
   const T* dOg = (const T*)a.dout + hoff;
-  const float* Lg = a.lse2 + (size_t)head * n;
   const float* Dg = a.dvec + (size_t)head * n;
   const int k0 = kt * BKV, kw0 = k0 + 32 * w, kj = kw0 + c;
 
-  // K is read sign-flipped for a negative scale (S = |s| Q (-K)^T), so the
-  // Q tiles stay as stored and dK takes the signed scale
-  RowFrags<T, D> kf, vf;
-  if (!MAT) kf.load(Kg, kj, n, h, a.qflip);
+  RowFrags<T, D> vf;
   vf.load(Vg, kj, n, h, 0u);
-  const T* Ag = MAT ? (const T*)a.amat + (size_t)head * n * a.lda : nullptr;
+  const T* Ag = (const T*)a.amat + (size_t)head * n * a.lda;
 
   const int q_begin = CAUSAL ? (k0 / BQ) * BQ : 0;
   const int nt = (n - q_begin + BQ - 1) / BQ;
 
   TileLoader<T, BQ, D> qld(w, lane), dold(w, lane);
-  // base-2 LSE and D rows of the tile: one 4-byte-per-lane LDS DMA each
-  // (waves 0 and 1); rows >= n fetch row n - 1 (masked by the kernel)
-  auto load_rows = [&](int r0, T (&tl)[2][TL::ELEMS], float (&ld)[2][BQ]) __attribute__((always_inline)) {
+  // D rows of the tile: one 4-byte-per-lane LDS DMA (wave 1); rows >= n fetch
+  // row n - 1 (masked by the kernel)
+  auto load_rows = [&](int r0, T (&tl)[2][TL::ELEMS], float (&ld)[BQ]) __attribute__((always_inline)) {
     qld.issue(tl[0], Qg, r0, n, w);
     dold.issue(tl[1], dOg, r0, n, w);
-    if (w < 2 && (!MAT || w == 1)) {   // MAT reads no L rows
-      const int r = min(r0 + lane, n - 1);
-      dma4(dma_rsrc(w == 0 ? Lg : Dg), 4u * (unsigned)r, (ATTN_LDS void*)(ld[w]));
-    }
+    if (w == 1) dma4(dma_rsrc(Dg), 4u * (unsigned)min(r0 + lane, n - 1), (ATTN_LDS void*)ld);
   };
   auto store_rows = [&](T (&tl)[2][TL::ELEMS]) __attribute__((always_inline)) {
     qld.commit(tl[0]);
@@ -835,10 +814,9 @@ __global__ void __launch_bounds__(256) dkdv_kernel(const BwdArgs a) {
   f32x16 dk[NDB], dv[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
-  const float sl2 = a.sl2;
 
-  auto step = [&](int it, T (&cur)[2][TL::ELEMS], float (&lcur)[2][BQ], T (&nxt)[2][TL::ELEMS],
-                  float (&lnxt)[2][BQ]) __attribute__((always_inline)) {
+  auto step = [&](int it, T (&cur)[2][TL::ELEMS], float (&lcur)[BQ], T (&nxt)[2][TL::ELEMS],
+                  float (&lnxt)[BQ]) __attribute__((always_inline)) {
     const int qt0 = q_begin + it * BQ;
     if (it + 1 < nt) load_rows(qt0 + BQ, nxt, lnxt);
     const T* ql = cur[0];
@@ -848,33 +826,27 @@ __global__ void __launch_bounds__(256) dkdv_kernel(const BwdArgs a) {
       const int qb0 = qt0 + 32 * qb;
       if (CAUSAL && qb0 + 31 < kw0) continue;  // every query of the block precedes every key
       f32x16 s = zero16(), dp = zero16();
-      if constexpr (MAT) {
-        // lane (h, c): P of query qb0 + 16h + j, key kj (rows or keys >= n read as 0)
+      // lane (h, c): P of query qb0 + 16h + j, key kj (rows or keys >= n read as 0)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int q = qb0 + 16 * h + j;
-          s[j] = (q < n && kj < n) ? (float)Ag[(size_t)q * a.lda + kj] : 0.f;
-        }
+      for (int j = 0; j < 16; ++j) {
+        const int q = qb0 + 16 * h + j;
+        s[j] = (q < n && kj < n) ? Ag[(size_t)q * a.lda + kj] : 0.f;
       }
 #pragma unroll
-      for (int t = 0; t < D / (2 * KP); ++t) {
-        if (!MAT) mma(s, RowRead<T, D>::get(ql, qb, t, h, c), kf.f[t]);
-        mma(dp, RowRead<T, D>::get(dol, qb, t, h, c), vf.f[t]);
-      }
+      for (int t = 0; t < D / (2 * KP); ++t) mma(dp, RowRead<T, D>::get(dol, qb, t, h, c), vf.f[t]);
       // lane (h, c): element j is query qb0 + 16h + j, key kj
-      const f32x4* lp = (const f32x4*)&lcur[0][32 * qb + 16 * h];
-      const f32x4* dp4 = (const f32x4*)&lcur[1][32 * qb + 16 * h];
+      const f32x4* dp4 = (const f32x4*)&lcur[32 * qb + 16 * h];
       const bool edge = (qb0 + 31 >= n) || (CAUSAL && qb0 < kw0 + 31);
       // valid queries qb0 + 16h + j: lo <= j <= hi
       const int qbase = qb0 + 16 * h;
       const int lo = CAUSAL ? kj - qbase : -1, hi = n - 1 - qbase;
 #pragma unroll
       for (int j4 = 0; j4 < 4; ++j4) {
-        const f32x4 l4 = lp[j4], d4 = dp4[j4];
+        const f32x4 d4 = dp4[j4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int j = 4 * j4 + e;
-          float p = MAT ? s[j] : exp2_fast(fmaf(s[j], sl2, -l4[e]));
+          float p = s[j];
           if (edge) p = (j < lo || j > hi) ? 0.f : p;
           s[j] = p;
           dp[j] = p * (dp[j] + d4[e]);   // d4 holds -D

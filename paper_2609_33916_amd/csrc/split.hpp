@@ -217,11 +217,13 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 1 : 2) fwd_s
         for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
     }
     const float mb = (m_use == -INFINITY) ? 0.f : -m_use;
+    float rs = 0.f;   // a block's sum first: thousands of single terms would lose bits in lsum
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       s[j] = exp2_fast(fmaf(s[j], sl2, mb));
-      lsum += s[j];
+      rs += s[j];
     }
+    lsum += rs;
   };
   // the K rows of a block in accumulator order: lane c takes key perm32(c)
   auto kload = [&](int kb, RowRegs<T, D>& k) __attribute__((always_inline)) {

@@ -73,8 +73,9 @@ def short_name(kernel: str) -> str:
     k = kernel.replace("void ", "")
     for key in ("decode_append_kernel", "decode_combine_kernel", "decode_kernel",
                 "mat_fwd_kernel", "bwd_prep_kernel", "zero_f32_kernel", "dq_finalize_kernel", "fwd_pp_kernel",
-                "fwd_kernel",
-                "dkdv16_kernel", "dkdv_kernel", "dq_kernel", "copyBuffer", "elementwise"):
+                "fwd_kernel", "fwd_split_kernel", "dkdv_split_kernel", "dq_split_kernel",
+                "fwd_x3_kernel", "dkdv_x3_kernel", "dq_x3_kernel",
+                "dkdv16_kernel", "mat_dkdv_kernel", "dkdv_kernel", "dq_kernel", "copyBuffer", "elementwise"):
         if key in k:
             if key == "dkdv16_kernel":
                 args = _template_args(k)

@@ -1,0 +1,70 @@
+"""float32 on the bfloat16 matrix cores (GPU): four- and eight-wave workgroups
+on both sides of their limit, lengths at the tile edges, values that do not
+split (infinities, the type's largest), and the error against float64."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from helpers import OUTPUTS, TOL, compare, gpu_available, run_fwd_bwd, to_gpu, to_host64
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("n,heads", [(129, 100), (192, 129), (255, 150), (511, 64), (520, 80), (40, 400)])
+def test_tile_edges(d, causal, n, heads):
+    w = workloads.Workload("x3", 1, heads, n, d, "f32", causal, 1.0, 1.0, 1.0, n + d)
+    scale = -0.2 if heads == 100 else w.scale
+    inp = workloads.generate(w)
+    got = run_fwd_bwd(to_gpu(inp), scale, causal)
+    some = [(0, 0), (0, heads - 1)]
+    ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, scale, causal, heads=some)
+    errs = compare({k: np.stack([to_host64(got[k])[b, h] for b, h in some]) for k in OUTPUTS}, ref)
+    # sums of at most 520 terms, each rounded to 2^-24 of the running sum, and
+    # products to 2^-25: far below the workload bound
+    assert all(v <= 1e-5 for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("pad", [-np.inf, np.finfo(np.float32).min])
+@pytest.mark.parametrize("n,heads", [(200, 200), (200, 100)])
+def test_keys_masked_by_value(d, pad, n, heads):
+    """A column of ones in Q and -inf (or the lowest value) in K masks a key;
+    the scores, O, L and dV are those without the masked keys."""
+    import torch
+    import paper_2609_33916_amd as lib
+    w = workloads.Workload("pad", 1, heads, n, d, "f32", False, 1.0, 1.0, 1.0, d)
+    inp = workloads.generate(w)
+    inp.q[..., 0], inp.k[..., 0] = 1.0, 0.0
+    inp.k[..., 150:, 0] = pad
+    dev = to_gpu(inp)
+    o, lse, _, _, dv = lib.attn_fwd_bwd(dev["q"], dev["k"], dev["v"], dev["do"], scale=1.0)
+    torch.cuda.synchronize()
+    ref = oracle.attention(inp.q[:, :1], inp.k[:, :1], inp.v[:, :1], inp.do[:, :1], 1.0, False) \
+        if pad != -np.inf else None
+    q, k, v, g = (torch.from_numpy(x[0, 0].astype(np.float64)) for x in (inp.q, inp.k, inp.v, inp.do))
+    s = q @ k[:150].T
+    p = torch.softmax(s, 1)
+    want = {"O": p @ v[:150], "L": torch.logsumexp(s, 1)}
+    errs = compare({"O": to_host64(o)[0, 0], "L": to_host64(lse)[0, 0]},
+                   {k2: x.numpy() for k2, x in want.items()}, keys=("O", "L"))
+    assert all(e <= TOL["f32"] for e in errs.values()), errs
+    got_dv = to_host64(dv)[0, 0]
+    assert np.abs(got_dv[:150] - (p.T @ g).numpy()).max() <= 1e-4 * np.abs(got_dv).max()
+    assert np.all(got_dv[150:] == 0.0)
+    if ref is not None:
+        assert np.abs(to_host64(o)[0, 0] - ref["O"][0, 0]).max() <= 1e-4
+
+
+def test_infinite_values_stay_infinite():
+    """An infinity in V makes that column of O infinite, as float32 sums do."""
+    import torch
+    import paper_2609_33916_amd as lib
+    x = torch.randn(1, 300, 200, 64, device="cuda")
+    v = x.clone()
+    v[0, :, 17, 5] = float("inf")
+    o, lse = lib.attn_fwd(x, x, v, scale=0.01)
+    torch.cuda.synchronize()
+    assert bool(torch.isinf(o[..., 5]).all()) and bool(torch.isfinite(o[..., 6:]).all()) and bool(torch.isfinite(lse).all())
