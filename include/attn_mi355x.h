@@ -248,7 +248,8 @@ int attn_mat_fwd_bwd(const void* Q, const void* K, const void* V, const void* dO
  * Work split: a workgroup owns one cache head, one split of its keys and up to
  * 32 of the query heads that read it, so each cache row is read once per
  * step; the keys are split (n + 1 rounded to 128-key tiles) until there are
- * about 512 workgroups, and a last pass merges the splits by log-sum-exp. The
+ * about 512 workgroups (short caches are not split), and a last pass merges
+ * the splits by log-sum-exp. The
  * merge needs attn_decode_workspace_bytes(...) bytes of 16-byte aligned
  * workspace (0 when the keys are not split; workspace may then be NULL). */
 size_t attn_decode_workspace_bytes(int B, int Hq, int Hkv, int n, int d, int append);

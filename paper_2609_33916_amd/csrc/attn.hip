@@ -182,10 +182,11 @@ void run_dispatch(int dtype, int d, int causal, Args a, int heads, hipStream_t s
 }
 
 // Decode: split plan. A workgroup owns (batch, cache head, up to 32 query
-// heads, one split of the keys); the keys are split until there are about two
-// workgroups per compute unit, each split a whole number of 128-key tiles.
+// heads, one split of the keys); the keys are split, into whole 128-key tiles,
+// until there are about two workgroups per compute unit, except in short
+// caches.
 struct DecodePlan {
-  int qchunks, nsplit, chunk;
+  int qchunks, nsplit;
 };
 constexpr int kDecodeTargetWGs = 512;
 DecodePlan decode_plan(int B, int Hq, int Hkv, int n, int append) {
@@ -197,8 +198,13 @@ DecodePlan decode_plan(int B, int Hq, int Hkv, int n, int append) {
   const long long tiles = std::max<long long>(1, (keys + 127) / 128);
   long long ns = std::max<long long>(1, (kDecodeTargetWGs + groups - 1) / groups);
   ns = std::min(ns, tiles);
-  const long long per = (tiles + ns - 1) / ns;     // tiles per split
-  p.chunk = (int)(per * 128);
+  // unsplit where the second pass (3 to 5 us) costs more than the longer chain:
+  // two tiles (1 sequence, 8 cache heads, n = 255: 9.1 us a step split, 8.2
+  // not; three tiles 9.2, 9.7), or a workgroup for every compute unit and up to
+  // 12 tiles (32 sequences, n = 767: 22.9 and 19.8; at n = 4096 with sequences
+  // of n/2 to n tokens 85 and 92, the splits even out their lengths)
+  if (tiles <= 2 || (groups >= 256 && tiles <= 12)) ns = 1;
+  const long long per = (tiles + ns - 1) / ns;     // most tiles of a split
   p.nsplit = (int)((tiles + per - 1) / per);
   return p;
 }
@@ -629,7 +635,7 @@ int attn_decode(const void* q, const void* k_new, const void* v_new, void* k_cac
   a.o = O; a.lse = L;
   a.rows = B * Hq;
   a.Hq = Hq; a.Hkv = Hkv; a.G = Hq / Hkv; a.n = n; a.n_cap = n_cap; a.append = append;
-  a.chunk = plan.chunk; a.nsplit = plan.nsplit; a.qchunks = plan.qchunks;
+  a.nsplit = plan.nsplit; a.qchunks = plan.qchunks;
   a.sl2 = sp.sl2;
   a.qflip = sp.qflip;
   hipStream_t st = static_cast<hipStream_t>(stream);

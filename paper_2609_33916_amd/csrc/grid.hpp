@@ -30,21 +30,21 @@ constexpr int kXcds = 8, kCusPerXcd = 32;
 ATTN_HD void block_map(int bid, int nblocks, int ntiles, int hgroup, bool reverse, int& head, int& tile) {
   int t;
   if (hgroup == 0) {
-    const int per = nblocks / kXcds;
+    const int per = (int)((unsigned)nblocks / kXcds);
     int lin = bid;
-    if (bid < per * kXcds) lin = (bid % kXcds) * per + bid / kXcds;
-    head = lin / ntiles;
+    if (bid < per * kXcds) lin = (bid & (kXcds - 1)) * per + (int)((unsigned)bid / kXcds);
+    head = (int)((unsigned)lin / (unsigned)ntiles);
     t = lin - head * ntiles;
   } else {
-    const int rem = nblocks / ntiles % hgroup, first = rem * ntiles;
+    const int rem = (int)((unsigned)nblocks / (unsigned)ntiles % (unsigned)hgroup), first = rem * ntiles;
     int h0 = 0, g = rem, i = bid;
     if (bid >= first) {
-      const int k = (bid - first) / (hgroup * ntiles);
+      const int k = (int)((unsigned)(bid - first) / (unsigned)(hgroup * ntiles));
       h0 = rem + k * hgroup;
       g = hgroup;
       i = bid - first - k * hgroup * ntiles;
     }
-    t = i / g;
+    t = (int)((unsigned)i / (unsigned)g);
     head = h0 + i - t * g;
   }
   tile = reverse ? ntiles - 1 - t : t;

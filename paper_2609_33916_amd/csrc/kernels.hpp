@@ -1522,7 +1522,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) dq_kernel(const B
 // decode_append_kernel writes the new token's key and value at row len_b of
 // its cache head. decode_kernel then covers keys [0, T_b) of every cache head
 // (T_b = len_b + 1 with an append): a workgroup owns one cache head, one
-// split of the keys (``chunk`` keys, a multiple of 128) and up to 32 of the
+// split of the keys (whole 128-key tiles) and up to 32 of the
 // query heads that share the cache head (GQA; MQA when there is one cache
 // head), so K and V are read once for the whole group. The group's queries
 // are the 32 columns of S^T = K Q^T (missing heads are zero columns); each
@@ -1544,7 +1544,7 @@ struct DecArgs {
   int rows;            // B * Hq
   int Hq, Hkv, G, n, n_cap, append;
   int fuse_append;     // decode_kernel writes the new row itself (one query chunk per cache head)
-  int chunk, nsplit, qchunks;
+  int nsplit, qchunks;
   float sl2;
   uint32_t qflip;
 };
@@ -1586,13 +1586,17 @@ __global__ void __launch_bounds__(256) decode_kernel(const DecArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int split = blockIdx.x;
+  const int split = (int)gridDim.x - 1 - (int)blockIdx.x;   // the last one, with the remainder, starts first
   const int grp = blockIdx.y;                        // (b, hk, qc)
   const int qc = grp % a.qchunks;
   const int bh = grp / a.qchunks;                    // b * Hkv + hk
   const int b = bh / a.Hkv, hk = bh % a.Hkv;
   const int T_b = dec_len(a, b) + a.append;
-  const int k_lo = split * a.chunk, k_hi = min(T_b, k_lo + a.chunk);
+  // the sequence's own tiles, evenly over the splits (a fixed chunk per split
+  // left the last one the remainder: 32 sequences of 2048 to 4096 tokens, two
+  // splits, 80.6 us a step, 74.3 so; 16 of 8191, 64 heads, 105.7 and 99.4)
+  const unsigned tiles = (unsigned)(T_b + 127) / 128u, ns = (unsigned)a.nsplit;
+  const int k_lo = 128 * (int)(split * (size_t)tiles / ns), k_hi = min(T_b, 128 * (int)((split + 1) * (size_t)tiles / ns));
   const int h0 = hk * a.G + qc * 32;                 // first query head of this workgroup
   const int nq = min(32, a.G - qc * 32);             // query heads in it
   const size_t kvoff = (size_t)bh * a.n_cap * D;
@@ -1623,7 +1627,10 @@ __global__ void __launch_bounds__(256) decode_kernel(const DecArgs a) {
     kload(kv0, kr);
   };
   // the workgroup whose split holds row len_b writes the new key and value
-  // there before any of its copies reads the row (no other workgroup reads it)
+  // there; only its own copies of the last tile read the row, after a barrier:
+  // the one below, or with a single tile one more. (A device-scope fence after
+  // the write, which nothing needs, wrote back the L2: 32 sequences, n = 255, 8
+  // cache heads 22.1 us a step, 12.6 without.)
   if (a.fuse_append) {
     const int pos = T_b - 1;
     if (pos >= k_lo && pos < k_hi) {
@@ -1633,9 +1640,8 @@ __global__ void __launch_bounds__(256) decode_kernel(const DecArgs a) {
         const T* src = (const T*)(which ? a.v_new : a.k_new) + (size_t)bh * D + 8 * ch;
         T* dst = (T*)(which ? a.vc : a.kc) + kvoff + (size_t)pos * D + 8 * ch;
         *(u32x4*)dst = *(const u32x4*)src;
-        __threadfence();
       }
-      __syncthreads();
+      if (nt == 1) __syncthreads();
     }
   }
   u32x4 kA[TD], kB[TD];
