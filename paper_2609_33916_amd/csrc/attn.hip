@@ -158,6 +158,19 @@ struct DkvL { static void run(attn::BwdArgs a, int heads, hipStream_t st) { laun
 template <typename T, int D, bool C>
 struct DqL { static void run(attn::BwdArgs a, int heads, hipStream_t st) { launch_dq<T, D, C>(a, heads, st); } };
 
+// dK/dV and dQ
+template <typename T, int D, bool C>
+struct BwdL {
+  static void run(attn::BwdArgs a, int heads, hipStream_t st) {
+    if (attn::one_backward(std::is_same<T, bf16>::value, D, C, heads, a.n)) {
+      attn::launch_bwd_split<T, D, C>(a, heads, st);
+    } else {
+      launch_dkdv<T, D, C>(a, heads, st);
+      launch_dq<T, D, C>(a, heads, st);
+    }
+  }
+};
+
 template <typename T, int D, bool C>
 struct MatFwdL { static void run(attn::FwdArgs a, int heads, hipStream_t st) { launch_mat_fwd<T, D, C>(a, heads, st); } };
 template <typename T, int D, bool C>
@@ -325,6 +338,10 @@ static int fwd_bwd_impl(const void* Q, const void* K, const void* V, const void*
   if (!mark(0)) return ATTN_E_HIP;
   run_dispatch<FwdL>(dtype, d, causal, f, B * H, st);
   if (hipGetLastError() != hipSuccess || !mark(1)) return ATTN_E_HIP;
+  if (!events) {
+    run_dispatch<BwdL>(dtype, d, causal, b, B * H, st);
+    return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_HIP;
+  }
   run_dispatch<DkvL>(dtype, d, causal, b, B * H, st);
   if (hipGetLastError() != hipSuccess || !mark(2)) return ATTN_E_HIP;
   run_dispatch<DqL>(dtype, d, causal, b, B * H, st);
@@ -391,9 +408,7 @@ int attn_bwd(const void* Q, const void* K, const void* V, const void* O, const f
   b.dk_scale = scale;
   b.dq_scale = scale;
   b.qflip = sp.qflip;
-  run_dispatch<DkvL>(dtype, d, causal, b, B * H, st);
-  if (hipGetLastError() != hipSuccess) return ATTN_E_HIP;
-  run_dispatch<DqL>(dtype, d, causal, b, B * H, st);
+  run_dispatch<BwdL>(dtype, d, causal, b, B * H, st);
   if (hipGetLastError() != hipSuccess) return ATTN_E_HIP;
   return ATTN_OK;
 }

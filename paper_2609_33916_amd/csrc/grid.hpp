@@ -87,7 +87,24 @@ constexpr int split_limit(Kind kind, bool b16, int d, bool causal) {
        {{384, 384}, {192, 224}, {128, 192}}}};
   return limit[b16][kind][d == 32 ? 0 : d == 64 ? 1 : 2][causal];
 }
+// The split kernels of the backward run in one launch (bwd_split_kernel) where
+// that is faster than two, and than the large-grid kernels: neither fills the
+// chip, so they run side by side, and a launch's fixed time is saved. Time of
+// two launches over one: 1.4-1.7 up to 32 tiles; bf16, d = 64, n = 512 / 2048 /
+// 8192: 64 tiles 1.32 / 1.29 / 1.31, 256 tiles 1.02 / 1.02 / 1.02, causal 256
+// tiles 1.12 / 1.29 / 1.42, 384 tiles 0.99 / 1.09; d = 128 (dK/dV takes a
+// compute unit's LDS) 96 tiles 1.24 / 1.25, 128 tiles 0.98 / 1.09 / 1.14, 192
+// tiles 0.73 / 0.83; float32, d = 64: 96 tiles 1.20 / 1.20, 128 tiles 0.95 /
+// 0.94 / 0.93.
+inline bool one_backward(bool b16, int d, bool causal, int heads, int n) {
+  constexpr int limit[2][3][2] = {   // [bf16][d = 32, 64, 128][causal]
+      {{104, 192}, {104, 176}, {104, 112}}, {{320, 384}, {256, 352}, {112, 128}}};
+  return (long long)heads * ((n + 127) / 128) <= limit[b16][d == 32 ? 0 : d == 64 ? 1 : 2][causal && n >= 512];
+}
+// (the backward kernels follow one_backward also where they are launched apart,
+// so that results do not depend on that)
 inline bool use_split(Kind kind, bool b16, int d, bool causal, int heads, int n) {
+  if (kind != kFwd && one_backward(b16, d, causal, heads, n)) return true;
   if (b16 && d == 128 && kind != kFwd && n <= 128) return false;
   return (long long)heads * ((n + 127) / 128) <= split_limit(kind, b16, d, causal && n >= 512);
 }

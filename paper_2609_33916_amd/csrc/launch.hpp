@@ -47,6 +47,7 @@ constexpr int kSplitRows = 32;
 template <typename T, int D, bool CAUSAL> void launch_fwd_split(FwdArgs a, int heads, hipStream_t st);
 template <typename T, int D, bool CAUSAL, bool AQ> void launch_dkdv_split(BwdArgs a, int heads, hipStream_t st);
 template <typename T, int D, bool CAUSAL> void launch_dq_split(BwdArgs a, int heads, hipStream_t st);
+template <typename T, int D, bool CAUSAL> void launch_bwd_split(BwdArgs a, int heads, hipStream_t st);   // both in one
 
 
 // The float32 kernels on the bfloat16 matrix cores (f32x3.hip).

@@ -17,10 +17,16 @@ template <typename T, int D, bool CAUSAL> void launch_dq_split(BwdArgs a, int he
   hipLaunchKernelGGL((dq_split_kernel<T, D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
 }
 
+template <typename T, int D, bool CAUSAL> void launch_bwd_split(BwdArgs a, int heads, hipStream_t st) {
+  set_grid(a, heads, kSplitRows, 2);
+  hipLaunchKernelGGL((bwd_split_kernel<T, D, CAUSAL>), dim3(2 * a.nblocks), dim3(256), 0, st, a);
+}
+
 #define ATTN_SPLIT_INST(T, D, C)                                    \
   template void launch_fwd_split<T, D, C>(FwdArgs, int, hipStream_t);  \
   template void launch_dkdv_split<T, D, C, false>(BwdArgs, int, hipStream_t); \
-  template void launch_dq_split<T, D, C>(BwdArgs, int, hipStream_t);
+  template void launch_dq_split<T, D, C>(BwdArgs, int, hipStream_t);   \
+  template void launch_bwd_split<T, D, C>(BwdArgs, int, hipStream_t);
 #define ATTN_SPLIT_INST_D(T, D) ATTN_SPLIT_INST(T, D, false) ATTN_SPLIT_INST(T, D, true)
 
 ATTN_SPLIT_INST_D(bf16, 32)

@@ -332,17 +332,15 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 1 : 2) fwd_s
 // P^T (dP^T - D), dQ^T += K^T dS^T; the waves' dQ are added.
 // ======================================================================
 template <typename T, int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 && D >= 64 ? 1 : 2) dq_split_kernel(const BwdArgs a) {
+__device__ __forceinline__ void dq_split(const BwdArgs& a, int bid, float* stA, float* stB) {
   constexpr int NDB = D / 32;
   constexpr bool B16 = sizeof(T) == 2;
   using MG = WaveMerge<D>;
-  __shared__ __attribute__((aligned(16))) float stA[MG::FLOATS];   // K tiles, as V's in the forward
-  __shared__ __attribute__((aligned(16))) float stB[MG::FLOATS];
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, qt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, CAUSAL, head, qt);
+  block_map(bid, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, CAUSAL, head, qt);
   const int n = a.n, q0 = 32 * qt, qi = q0 + c;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Kg = (const T*)a.k + hoff;
@@ -453,26 +451,24 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 && D >= 64 ? 1 : 2) dq_spl
 // passes its dS through an LDS tile [keys][queries] to form dQ = dS K of the
 // block, added to the float32 accumulator with atomic adds.
 // ======================================================================
-template <typename T, int D, bool CAUSAL, bool AQ = false>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 || D == 128 ? 1 : 2) dkdv_split_kernel(const BwdArgs a) {
+template <typename T, int D, bool AQ> struct DkdvLds {
+  // bf16: Q tiles, then dO tiles of the four waves, per stage
+  static constexpr int STF = WaveMerge<D>::FLOATS * (sizeof(T) == 2 ? 2 : 1);
+  static constexpr int KBL = AQ ? 32 * D : 8;     // AQ: the workgroup's K rows
+  static constexpr int DST = AQ ? 32 * 32 : 8;    // AQ: each wave's dS^T
+};
+template <typename T, int D, bool CAUSAL, bool AQ>
+__device__ __forceinline__ void dkdv_split(const BwdArgs& a, int bid, float* stA, float* stB, float (&ldA)[4][2][64],
+                                           float (&ldB)[4][2][64], bf16* kbl, bf16 (*dst)[DkdvLds<T, D, AQ>::DST]) {
   static_assert(!AQ || sizeof(T) == 2, "the atomic-dQ form is bf16");
   constexpr int NDB = D / 32;
   constexpr bool B16 = sizeof(T) == 2;
   using MG = WaveMerge<D>;
-  // bf16: Q tiles, then dO tiles of the four waves, two stages
-  constexpr int STF = MG::FLOATS * (B16 ? 2 : 1);
-  __shared__ __attribute__((aligned(16))) float stA[STF];
-  __shared__ __attribute__((aligned(16))) float stB[STF];
-  // base-2 log-sum-exp and -D rows of each wave's block
-  __shared__ __attribute__((aligned(16))) float ldA[4][2][64];
-  __shared__ __attribute__((aligned(16))) float ldB[4][2][64];
-  __shared__ __attribute__((aligned(16))) bf16 kbl[AQ ? 32 * D : 8];         // AQ: the workgroup's K rows
-  __shared__ __attribute__((aligned(16))) bf16 dst[4][AQ ? 32 * 32 : 8];     // AQ: each wave's dS^T
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int head, kt;
-  block_map(blockIdx.x, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, false, head, kt);
+  block_map(bid, a.nblocks, a.ntiles, CAUSAL ? a.hgroup : 0, false, head, kt);
   const int n = a.n, k0 = 32 * kt, kj = k0 + c;
   const size_t hoff = (size_t)head * (size_t)a.head_stride;
   const T* Qg = (const T*)a.q + hoff;
@@ -639,6 +635,39 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 || D == 128 ? 1 : 2) dkdv_
   };
   merge(dv, a.dv, 1.f);
   merge(dk, a.dk, a.dk_scale);
+}
+
+// The backward's kernels. bwd_split_kernel runs both in one launch, the dK/dV
+// workgroups first.
+template <typename T, int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 && D >= 64 ? 1 : 2) dq_split_kernel(const BwdArgs a) {
+  // K tiles in two distinct LDS objects, as V's in the forward
+  __shared__ __attribute__((aligned(16))) float stA[WaveMerge<D>::FLOATS];
+  __shared__ __attribute__((aligned(16))) float stB[WaveMerge<D>::FLOATS];
+  dq_split<T, D, CAUSAL>(a, blockIdx.x, stA, stB);
+}
+template <typename T, int D, bool CAUSAL, bool AQ>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 || D == 128 ? 1 : 2) dkdv_split_kernel(const BwdArgs a) {
+  using L = DkdvLds<T, D, AQ>;
+  __shared__ __attribute__((aligned(16))) float stA[L::STF];
+  __shared__ __attribute__((aligned(16))) float stB[L::STF];
+  // base-2 log-sum-exp and -D rows of each wave's block
+  __shared__ __attribute__((aligned(16))) float ldA[4][2][64];
+  __shared__ __attribute__((aligned(16))) float ldB[4][2][64];
+  __shared__ __attribute__((aligned(16))) bf16 kbl[L::KBL];
+  __shared__ __attribute__((aligned(16))) bf16 dst[4][L::DST];
+  dkdv_split<T, D, CAUSAL, AQ>(a, blockIdx.x, stA, stB, ldA, ldB, kbl, dst);
+}
+template <typename T, int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 || D == 128 ? 1 : 2) bwd_split_kernel(const BwdArgs a) {
+  using L = DkdvLds<T, D, false>;
+  __shared__ __attribute__((aligned(16))) float stA[L::STF];
+  __shared__ __attribute__((aligned(16))) float stB[L::STF];
+  __shared__ __attribute__((aligned(16))) float ldA[4][2][64];
+  __shared__ __attribute__((aligned(16))) float ldB[4][2][64];
+  const int bid = blockIdx.x;
+  if (bid < a.nblocks) dkdv_split<T, D, CAUSAL, false>(a, bid, stA, stB, ldA, ldB, nullptr, nullptr);
+  else dq_split<T, D, CAUSAL>(a, bid - a.nblocks, stA, stB);
 }
 
 }  // namespace attn

@@ -37,3 +37,28 @@ def test_both_sides_of_the_limits(heads):
         host = {k: np.stack([to_host64(got[k])[b, h] for b, h in some]) for k in OUTPUTS}
         errs = compare(host, ref)
         assert all(v <= TOL[dtype] for v in errs.values()), (dtype, d, causal, errs)
+
+
+@pytest.mark.parametrize("dtype,d,causal,heads", [("bf16", 128, False, 29), ("bf16", 128, True, 33), ("bf16", 64, False, 65),
+                                                  ("f32", 64, False, 26), ("f32", 64, False, 27)])
+def test_one_launch_equals_two(dtype, d, causal, heads):
+    """Around the limits of the one-launch backward: attn_fwd_bwd and the timed
+    form, which launches dK/dV and dQ apart, give the same bits, and both hold
+    against float64."""
+    import torch
+    import paper_2609_33916_amd as lib
+    from bench import HipEvents
+    for h in (heads - 1, heads):
+        w = workloads.Workload("one", 1, h, 512, d, dtype, causal, 1.0, 1.0, 1.0, h)
+        inp = workloads.generate(w)
+        dev = to_gpu(inp)
+        got = run_fwd_bwd(dev, w.scale, causal)
+        ev = HipEvents()
+        marks = [ev.create() for _ in range(4)]
+        two = lib.attn_fwd_bwd_timed(dev["q"], dev["k"], dev["v"], dev["do"], marks, scale=w.scale, causal=causal)
+        torch.cuda.synchronize()
+        assert all(torch.equal(got[k], x) for k, x in zip(OUTPUTS, two))
+        some = [(0, 0), (0, h - 1)]
+        ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, causal, heads=some)
+        errs = compare({k: np.stack([to_host64(got[k])[b, x] for b, x in some]) for k in OUTPUTS}, ref)
+        assert all(v <= TOL[dtype] for v in errs.values()), errs
