@@ -129,8 +129,20 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(const PrepArgs a) {
 // Per wave and key tile:  S^T = K Q^T (rows = keys, cols = the wave's 32
 // queries), online softmax per column, O^T += V^T P^T.
 // ======================================================================
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdArgs a) {
+// P is held as 2^(S sl2 - m - kPShift), so that it reaches 2, and with it bit 14
+// of its bfloat16 pattern, when S sl2 exceeds m by kRescaleThresh: the OR of a
+// tile's operands says whether the maximum has to move, and the tile's own
+// maximum is only formed then (infinities and NaN have that bit too). VALU
+// issue bounds this kernel (75 % of its cycles, matrix cores 44 %), and the OR is
+// 8 instructions where the maximum is 22. 128 heads, n = 4096, forward before /
+// after: d = 32 407 / 382 us, causal 215 / 203; d = 64 606 / 598, causal 325 /
+// 321; n = 1537, 48 heads, d = 64 53.0 / 51.1. LAZY = false forms every tile's
+// maximum: at d = 64 it needs 40 registers less (four waves per SIMD instead of
+// three), which one tile per workgroup gains more from (1000 heads, n = 64:
+// 12.4 against 14.0 us).
+constexpr float kPShift = kRescaleThresh - 1.f;
+template <int D, bool CAUSAL, bool LAZY>
+__global__ void __launch_bounds__(256, LAZY ? 2 : 4) fwd_kernel(const FwdArgs a) {
   using T = bf16;
   using E = Elem<T>;
   using Frag = typename E::frag;
@@ -185,51 +197,71 @@ __global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdArgs a) {
       const T* kl = cur[0];
       const T* vl = cur[1];
       f32x16 s[NKB];
-#pragma unroll
-      for (int b = 0; b < NKB; ++b) {
-        s[b] = zero16();
-#pragma unroll
-        for (int t = 0; t < TD; ++t) mma(s[b], RowRead<T, D>::get(kl, b, t, h, c), qf.f[t]);
-      }
-      // lane (h, c): s[b][j] = raw score of key kv0 + 32b + 16h + j, query qi
-      const bool edge = (kv0 + BKV > n) || (CAUSAL && kv0 + BKV - 1 > qw0);
-      if (edge) {
-        // keys after `last` are masked; the lane's keys of block b are base_b + j
-        const int last = CAUSAL ? min(qi, n - 1) : n - 1;
+      auto scores = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < NKB; ++b) {
-          const int lim = last - (kv0 + 32 * b + 16 * h);
+          s[b] = zero16();
 #pragma unroll
-          for (int j = 0; j < 16; ++j) s[b][j] = (j > lim) ? -INFINITY : s[b][j];
+          for (int t = 0; t < TD; ++t) mma(s[b], RowRead<T, D>::get(kl, b, t, h, c), qf.f[t]);
         }
-      }
-      float mx = -INFINITY;
+        // lane (h, c): s[b][j] = raw score of key kv0 + 32b + 16h + j, query qi
+        const bool edge = (kv0 + BKV > n) || (CAUSAL && kv0 + BKV - 1 > qw0);
+        if (edge) {
+          // keys after `last` are masked; the lane's keys of block b are base_b + j
+          const int last = CAUSAL ? min(qi, n - 1) : n - 1;
 #pragma unroll
-      for (int b = 0; b < NKB; ++b)
+          for (int b = 0; b < NKB; ++b) {
+            const int lim = last - (kv0 + 32 * b + 16 * h);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[b][j]);
-      mx = halves_max(mx);
-      const float mt = mx * sl2;
-      const bool resc = mt > m_use + kRescaleThresh;
-      if (__builtin_amdgcn_ballot_w64(resc)) {
-        const float alpha = resc ? exp2_fast(m_use - mt) : 1.f;
-        if (resc) m_use = mt;
-        lsum *= alpha;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
-      }
-      const float mb = (m_use == -INFINITY) ? 0.f : -m_use;
-      float rs = 0.f;
-#pragma unroll
-      for (int b = 0; b < NKB; ++b)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const float p = exp2_fast(fmaf(s[b][j], sl2, mb));
-          rs += p;
-          s[b][j] = p;
+            for (int j = 0; j < 16; ++j) s[b][j] = (j > lim) ? -INFINITY : s[b][j];
+          }
         }
+      };
+      scores();
+      // P of the tile as operands, its sum, and the OR of its bit patterns
+      Frag pf[NKB][T32];
+      float rs;
+      auto exps = [&](float mb) __attribute__((always_inline)) -> uint32_t {
+        uint32_t bits = 0;
+        rs = 0.f;
+#pragma unroll
+        for (int b = 0; b < NKB; ++b) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            s[b][j] = exp2_fast(fmaf(s[b][j], sl2, mb));
+            rs += s[b][j];
+          }
+#pragma unroll
+          for (int t = 0; t < T32; ++t) {
+            pf[b][t] = FragFromAcc<T>::get(s[b], t);
+            const u32x4 u = __builtin_bit_cast(u32x4, pf[b][t]);
+            bits |= u[0] | u[1] | u[2] | u[3];
+          }
+        }
+        return bits;
+      };
+      // (the first tile always sets the maximum)
+      if (!LAZY || it == 0 || __builtin_amdgcn_ballot_w64((exps(-kPShift - m_use) & 0x40004000u) != 0)) {
+        if (LAZY && it > 0) scores();   // again, K being at hand: kept, they would cost registers
+        float mx = -INFINITY;
+#pragma unroll
+        for (int b = 0; b < NKB; ++b)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[b][j]);
+        mx = halves_max(mx);
+        const float mt = mx * sl2;
+        const bool resc = mt > m_use + kRescaleThresh;
+        if (__builtin_amdgcn_ballot_w64(resc)) {
+          const float alpha = resc ? exp2_fast(m_use - mt) : 1.f;
+          if (resc) m_use = mt;
+          lsum *= alpha;
+#pragma unroll
+          for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
+        }
+        exps(m_use == -INFINITY ? 0.f : -kPShift - m_use);
+      }
       lsum += rs;
       // the PV products at a raised wave priority (forward 1-3 % faster;
       // raising it for the score products and exponentials instead, as in
@@ -239,10 +271,9 @@ __global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdArgs a) {
       for (int b = 0; b < NKB; ++b)
 #pragma unroll
         for (int t = 0; t < T32; ++t) {
-          const Frag pf = FragFromAcc<T>::get(s[b], t);
 #pragma unroll
           for (int db = 0; db < NDB; ++db)
-            mma(oacc[db], TransRead<T, D>::get(vl, b, db, t, h, c), pf);
+            mma(oacc[db], TransRead<T, D>::get(vl, b, db, t, h, c), pf[b][t]);
         }
       __builtin_amdgcn_s_setprio(0);
     }
@@ -283,7 +314,7 @@ __global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdArgs a) {
   const float dsum = halves_sum(dpart);
   if (qi < n && h == 0) {
     const size_t row = (size_t)head * n + qi;
-    const float l2 = m_use + log2f(ltot);
+    const float l2 = m_use + (kPShift + log2f(ltot));
     a.lse[row] = l2 * kLn2;
     if (dOg) {
       a.dvec[row] = -dsum;   // stored negated (the backward starts dP - D from it)
