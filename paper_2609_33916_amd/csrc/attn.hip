@@ -140,9 +140,18 @@ void launch_dkdv_aq(attn::BwdArgs a, int heads, hipStream_t st) {
   }
 }
 
+// In bf16 the materialising forward is bound by memory, its K and V reads
+// competing with the stores of P: under the causal mask it takes the heads one
+// by one where the K and V of a group's heads on one XCD outgrow the 4 MB L2.
+// Grouped / head by head, d = 64: 128 heads, n = 4096 1003 / 906 us, 64 heads
+// 506 / 490 (8 MB), but 32 heads 263 / 324 (4 MB); d = 128, 128 heads, n = 4096
+// 1227 / 1211. Float32, whose products bound it, 128 heads, n = 2048: 1002 /
+// 1284.
 template <typename T, int D, bool CAUSAL>
 void launch_mat_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
   attn::set_grid(a, heads, kFwdBQ, fwd_per_cu<T>(D));
+  const long long kv = (a.hgroup + attn::kXcds - 1) / attn::kXcds * 2LL * a.n * D * (long long)sizeof(T);
+  if (std::is_same<T, bf16>::value && kv > (4 << 20)) a.hgroup = 0;
   hipLaunchKernelGGL((attn::mat_fwd_kernel<T, D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
 }
 
