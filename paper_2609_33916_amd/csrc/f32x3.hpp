@@ -8,12 +8,13 @@
 // at 1/16 of the bfloat16 rate, so six cost 0.375 of one. Softmax, dS and all
 // sums stay in float32.
 //
-// Infinities, and values that bfloat16 would round to infinity, do not split.
-// Every tile and a wave's own rows are tested for them (a maximum per value),
-// and a workgroup that meets one starts over on the float32 matrix instructions
-// with operands straight from memory: results there are those of float32
-// arithmetic. NaN splits into NaN, and dS beyond the float32 range, which gave
-// infinities or NaN in dQ and dK, gives NaN.
+// Infinities do not split, nor do values that bfloat16 would round to infinity,
+// and part products of large values overflow on their own (kSplitMax). Every
+// tile and a wave's own rows are tested for such values (a maximum per value),
+// and the accumulators at the end for infinities and NaN, which P or dS beyond
+// the range leave there (attn_bwd takes any L and O). A workgroup that meets
+// either starts over on the float32 matrix instructions with operands straight
+// from memory: results there are those of float32 arithmetic.
 //
 // Measured (us, float32 matrix instructions / these; MI355X): 64 heads, n =
 // 2048, d = 64: forward 557 / 390, dK/dV 1190 / 706, dQ 891 / 520; d = 128:
@@ -56,9 +57,12 @@ __device__ __forceinline__ Parts split3(const f32x16& v, int t) {
   for (int i = 0; i < 8; ++i) x[i] = v[8 * t + i];
   return split3(x);
 }
-// A maximum of absolute values from here on (2^128 - 2^119, rounds to infinity
-// in bfloat16) means that something does not split.
-constexpr float kSplitMax = 0x1.ffp127f;
+// Operands below this bound split, and neither their part products nor what the
+// kernels form from them leaves the float32 range: scores and dP stay below
+// 2^55, dS, with P <= 1, below 2^57, and sums over 2^20 rows of it below 2^101.
+// From the bound on a product can overflow while a part product of the other
+// sign does too, to NaN where float32 arithmetic gives an infinity.
+constexpr float kSplitMax = 0x1p24f;
 __device__ __forceinline__ float absmax8(float m, const f32x8& x) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
@@ -178,6 +182,21 @@ template <int NW> __device__ __forceinline__ bool any_flag(const int (&f)[NW]) {
   for (int i = 0; i < NW; ++i) r |= f[i];
   return __builtin_amdgcn_readfirstlane(r) != 0;
 }
+// whether an accumulator of this wave holds an infinity or NaN
+template <int N> __device__ __forceinline__ bool any_nonfinite(const f32x16 (&a)[N]) {
+  float x = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x = fmaf(a[i][j], 0.f, x);
+  return __builtin_amdgcn_ballot_w64(x != 0.f) != 0;   // NaN from either
+}
+// whether any wave of the workgroup has `f`
+template <int NW> __device__ __forceinline__ bool any_wave(int (&flag)[NW], int wv, int lane, bool f) {
+  if (lane == 0) flag[wv] = f;
+  __syncthreads();
+  return any_flag(flag);
+}
 template <int D, int ROWS> __device__ __forceinline__ Parts row_parts(const bf16* s, int rb, int t, int h, int c) {
   return {RowRead<bf16, D>::get(s, rb, t, h, c), RowRead<bf16, D>::get(s + ROWS * D, rb, t, h, c),
           RowRead<bf16, D>::get(s + 2 * ROWS * D, rb, t, h, c)};
@@ -200,6 +219,7 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
   constexpr int TILES = 2 * 3 * ST::ELEMS * 2;
   __shared__ __attribute__((aligned(16))) bf16 st[(TILES > MERGE ? TILES : MERGE) / 2];
   __shared__ int flag[4 * KS];   // per wave: its part of the tile does not split
+  __shared__ int bad[4 * KS];    // per wave: its accumulators are not finite
   bf16* const kl = st;
   bf16* const vl = st + 3 * ST::ELEMS;
 
@@ -297,6 +317,7 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
       }
   }
 
+  if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(oacc));
   if (slow) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) oacc[db] = zero16();
@@ -384,6 +405,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
   constexpr int TILES = 2 * 3 * ST::ELEMS * 2;
   __shared__ __attribute__((aligned(16))) bf16 st[(TILES > MERGE ? TILES : MERGE) / 2];
   __shared__ int flag[4 * KS];   // per wave: its part of the tile does not split
+  __shared__ int bad[4 * KS];    // per wave: its accumulators are not finite
   bf16* const kl = st;
   bf16* const vl = st + 3 * ST::ELEMS;
 
@@ -456,6 +478,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
     }
   }
 
+  if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(dqa));
   if (slow) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) dqa[db] = zero16();
@@ -509,6 +532,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
   constexpr int TILES = 2 * 3 * ST::ELEMS * 2;
   __shared__ __attribute__((aligned(16))) bf16 st[(TILES > MERGE ? TILES : MERGE) / 2];
   __shared__ int flag[4 * KS];   // per wave: its part of the tile does not split
+  __shared__ int bad[4 * KS];    // per wave: its accumulators are not finite
   __shared__ __attribute__((aligned(16))) float ld[2][BT];   // the tile's L and -D rows
   bf16* const ql = st;
   bf16* const ol = st + 3 * ST::ELEMS;
@@ -597,6 +621,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
     }
   }
 
+  if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(dk) || any_nonfinite(dv));
   if (slow) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }

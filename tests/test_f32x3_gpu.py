@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import workloads
-from helpers import OUTPUTS, TOL, compare, gpu_available, run_fwd_bwd, to_gpu, to_host64
+from helpers import OUTPUTS, TOL, compare, gpu_available, max_rel, run_fwd_bwd, to_gpu, to_host64
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
 
@@ -56,6 +56,59 @@ def test_keys_masked_by_value(d, pad, n, heads):
     assert np.all(got_dv[150:] == 0.0)
     if ref is not None:
         assert np.abs(to_host64(o)[0, 0] - ref["O"][0, 0]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("qcol,pad", [(1e4, -1.1e38), (100300.0, -1e38), (2.0 ** 25, -2.0 ** 109)])
+def test_keys_masked_by_an_overflowing_product(d, causal, qcol, pad):
+    """Finite operands whose product leaves the float32 range: the score is
+    -inf, as the float32 product is, although a part product of the other sign
+    overflows too; such a key is masked and nothing becomes NaN."""
+    n, heads, tail = 200, 200, 150
+    w = workloads.Workload("over", 1, heads, n, d, "f32", causal, 1.0, 1.0, 1.0, d)
+    inp = workloads.generate(w)
+    inp.q[..., 0], inp.k[..., 0] = qcol, 0.0
+    inp.k[..., tail:, 0] = pad
+    scale = 0.2
+    got = run_fwd_bwd(to_gpu(inp), scale, causal)
+    for head in (0, heads - 1):
+        q, k, v, g = (x[0, head].astype(np.float64) for x in (inp.q, inp.k, inp.v, inp.do))
+        s = scale * q[:, 1:] @ k[:, 1:].T
+        s[:, tail:] = -np.inf
+        if causal:
+            s[np.triu_indices(n, 1)] = -np.inf
+        lse = np.log(np.exp(s).sum(1))
+        p = np.exp(s - lse[:, None])
+        o = p @ v
+        ds = p * (g @ v.T - (g * o).sum(1)[:, None]) * scale
+        ref = {"O": o, "L": lse, "dQ": ds[:, :tail] @ k[:tail], "dK": ds.T @ q, "dV": p.T @ g}
+        errs = compare({key: to_host64(got[key])[0, head] for key in OUTPUTS}, ref)
+        # dK's first column sums 200 terms of about qcol that nearly cancel
+        assert all(e <= TOL["f32"] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("lse,do,v", [(0.0, 1.5e19, 3.4e38 / 1.5e19), (-60.0, 1.8e6, 3.4e38 / 1.8e6 / np.exp(60.0))])
+def test_dS_up_to_the_largest_float(d, causal, lse, do, v):
+    """dS = 3.4e38, which bfloat16 rounds to infinity, gives the dQ that float32
+    gives (O = 0, so that D = 0; Q = 0 and the given L make P exp(-L))."""
+    import torch
+    import paper_2609_33916_amd as lib
+    n, heads = 200, 200
+    q, o = torch.zeros(1, heads, n, d, device="cuda"), torch.zeros(1, heads, n, d, device="cuda")
+    k = torch.full_like(q, 2.0 ** -10)
+    vt, g = torch.zeros_like(q), torch.zeros_like(q)
+    vt[..., 0], g[..., 0] = v, do
+    dq, dk, dv = lib.attn_bwd(q, k, vt, o, torch.full((1, heads, n), lse, device="cuda"), g, scale=1.0, causal=causal)
+    torch.cuda.synchronize()
+    keys = np.arange(1, n + 1) if causal else np.full(n, n)
+    want = np.exp(-lse) * float(np.float32(do)) * float(np.float32(v)) * 2.0 ** -10 * keys[:, None] * np.ones(d)
+    assert max_rel(to_host64(dq)[0, 0], want) <= TOL["f32"] and max_rel(to_host64(dq)[0, -1], want) <= TOL["f32"]
+    want = np.exp(-lse) * float(np.float32(do)) * (n - np.arange(n) if causal else np.full(n, n))
+    assert max_rel(to_host64(dv)[0, 0, :, 0], want) <= TOL["f32"]
+    assert bool((dk == 0).all())
 
 
 def test_infinite_values_stay_infinite():
