@@ -1,6 +1,7 @@
 // float32 kernels on the bfloat16 matrix cores: every operand is split into
 // three bfloat16 parts, x = hi + mid + lo (8 + 8 + 8 significand bits, each
-// part rounded to nearest, so nothing of x is lost), and a product is the six
+// part rounded to nearest, so that nothing of an x of 2^-110 or more is lost;
+// below, lo falls under the smallest bfloat16), and a product is the six
 // part products down to 2^-16 of the largest (hi hi, hi mid, mid hi, mid mid,
 // hi lo, lo hi), accumulated in float32, the small ones first. What is left
 // out (mid lo, lo mid, lo lo) is below 2^-25 of a product, less than the
@@ -8,13 +9,13 @@
 // at 1/16 of the bfloat16 rate, so six cost 0.375 of one. Softmax, dS and all
 // sums stay in float32.
 //
-// Infinities do not split, nor do values that bfloat16 would round to infinity,
-// and part products of large values overflow on their own (kSplitMax). Every
-// tile and a wave's own rows are tested for such values (a maximum per value),
-// and the accumulators at the end for infinities and NaN, which P or dS beyond
-// the range leave there (attn_bwd takes any L and O). A workgroup that meets
-// either starts over on the float32 matrix instructions with operands straight
-// from memory: results there are those of float32 arithmetic.
+// Infinities do not split, nor do values below 2^-110 other than 0, and part
+// products of large values overflow on their own (Range). Every tile and a
+// wave's own rows are tested for such values, and the accumulators at the end
+// for infinities and NaN, which P or dS beyond the range leave there (attn_bwd
+// takes any L and O). A workgroup that meets either starts over on the float32
+// matrix instructions with operands straight from memory: results there are
+// those of float32 arithmetic.
 //
 // Measured (us, float32 matrix instructions / these; MI355X): 64 heads, n =
 // 2048, d = 64: forward 557 / 390, dK/dV 1190 / 706, dQ 891 / 520; d = 128:
@@ -57,18 +58,34 @@ __device__ __forceinline__ Parts split3(const f32x16& v, int t) {
   for (int i = 0; i < 8; ++i) x[i] = v[8 * t + i];
   return split3(x);
 }
-// Operands below this bound split, and neither their part products nor what the
-// kernels form from them leaves the float32 range: scores and dP stay below
-// 2^55, dS, with P <= 1, below 2^57, and sums over 2^20 rows of it below 2^101.
-// From the bound on a product can overflow while a part product of the other
-// sign does too, to NaN where float32 arithmetic gives an infinity.
-constexpr float kSplitMax = 0x1p24f;
-__device__ __forceinline__ float absmax8(float m, const f32x8& x) {
+// P and dS, whose small values are ordinary, are formed 2^24 times as large and
+// the accumulators scaled back at the end: all of their normal values (2^-126 on)
+// then split without loss, and dS's subnormal ones too. (The matrix cores take and
+// give subnormals.)
+constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
+// Whether values split: 0, or kSplitMin <= |x| < kSplitMax. Under kSplitMax
+// neither part products nor what the kernels form from them leave the float32
+// range: scores and dP stay below 2^55, dS, with P <= 1, below 2^57, 2^24 dS
+// below 2^81, and sums of it over 2^20 rows below 2^125. From there on a product
+// can overflow while a part product of the other sign does too, to NaN where
+// float32 arithmetic gives an infinity.
+struct Range {
+  static constexpr float kSplitMax = 0x1p24f;
+  static constexpr uint32_t kSplitMin = 17u << 23;   // bits of 2^-110
+  float mx = 0.f;
+  uint32_t mn = ~0u;   // least 2 bits(|x|) - 1, of which 0 gives the largest
+  __device__ __forceinline__ void add(const f32x8& x) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
-  return m;
-}
-__device__ __forceinline__ bool any_huge(float m) { return __builtin_amdgcn_ballot_w64(m >= kSplitMax) != 0; }
+    for (int i = 0; i < 8; ++i) {
+      mx = fmaxf(mx, fabsf(x[i]));
+      mn = min(mn, (__float_as_uint(x[i]) << 1) - 1u);
+    }
+  }
+  // whether a lane of the wave has met a value that does not split
+  __device__ __forceinline__ bool left() const {
+    return __builtin_amdgcn_ballot_w64(mx >= kSplitMax || mn < 2u * kSplitMin - 1u) != 0;
+  }
+};
 // The float32 products for inputs that do not split.
 // acc += A B^T over d: rows arow of A and brow of B (zeros from row n on), B's
 // signs flipped by `flip`.
@@ -115,12 +132,13 @@ __device__ __forceinline__ f32x8 as_f32x8(u32x4 a, u32x4 b) {
 }
 
 // Row operands of one row per lane: k-step t holds columns 16t + 8h + [0, 8).
-// load() returns whether the wave's rows hold something that does not split.
+// load() returns whether the wave's rows hold something that does not split,
+// and takes a power of two to multiply the rows by.
 template <int D> struct RowParts {
   Parts f[D / 16];
-  __device__ __forceinline__ bool load(const float* g, int row, int n, int h, uint32_t flip) {
+  __device__ __forceinline__ bool load(const float* g, int row, int n, int h, uint32_t flip, float up = 1.f) {
     f32x8 x[D / 16];
-    float m = 0.f;
+    Range m;
 #pragma unroll
     for (int t = 0; t < D / 16; ++t) {
       u32x4 a = {0u, 0u, 0u, 0u}, b = a;
@@ -130,11 +148,11 @@ template <int D> struct RowParts {
         b = p[1] ^ (u32x4){flip, flip, flip, flip};
       }
       x[t] = as_f32x8(a, b);
-      m = absmax8(m, x[t]);
+      m.add(x[t]);
     }
 #pragma unroll
-    for (int t = 0; t < D / 16; ++t) f[t] = split3(x[t]);
-    return any_huge(m);
+    for (int t = 0; t < D / 16; ++t) f[t] = split3(x[t] * up);
+    return m.left();
   }
 };
 
@@ -165,14 +183,14 @@ template <int ROWS, int D, int NT> struct Stage3 {
   }
   // returns whether the wave's part holds something that does not split
   __device__ __forceinline__ bool store(bf16* lds, int tid) const {
-    float m = 0.f;
+    Range m;
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
       const f32x8 x = as_f32x8(r[i][0], r[i][1]);
-      m = absmax8(m, x);
+      m.add(x);
       put(lds, tid + NT * i, split3(x));
     }
-    return any_huge(m);
+    return m.left();
   }
 };
 // whether any of the NW waves set its flag
@@ -246,8 +264,8 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
   for (int db = 0; db < NDB; ++db) oacc[db] = zero16();
   float m_use = -INFINITY, lsum = 0.f;
   const float sl2 = a.sl2;
-  // scores of the keys from kv0 on -> P, moving the running maximum and sum
-  auto softmax = [&](int kv0, auto& s) __attribute__((always_inline)) {
+  // scores of the keys from kv0 on -> up P, moving the running maximum and sum
+  auto softmax = [&](int kv0, auto& s, float up) __attribute__((always_inline)) {
     constexpr int B = sizeof(s) / sizeof(f32x16);
     if (kv0 + 32 * B > n || (CAUSAL && kv0 + 32 * B - 1 > qw0)) {
       const int last = CAUSAL ? min(qi, n - 1) : n - 1;
@@ -280,7 +298,7 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
     for (int b = 0; b < B; ++b)
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        s[b][j] = exp2_fast(fmaf(s[b][j], sl2, mb));
+        s[b][j] = exp2_fast(fmaf(s[b][j], sl2, mb)) * up;
         rs += s[b][j];
       }
     lsum += rs;
@@ -306,7 +324,7 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
     for (int t = 0; t < D / 16; ++t)
 #pragma unroll
       for (int b = 0; b < NB; ++b) mma6(s[b], row_parts<D, BT>(kl, NB * ks + b, t, h, c), q.f[t]);
-    softmax(kv0, s);
+    softmax(kv0, s, kUp);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -317,7 +335,13 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
       }
   }
 
+  __builtin_amdgcn_sched_barrier(0);   // keeps the test out of the loop's schedule (35 more spills without)
   if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(oacc));
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) oacc[db][j] *= kDown;
+  lsum *= kDown;
   if (slow) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) oacc[db] = zero16();
@@ -326,7 +350,7 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
     for (int kv0 = 32 * ks; kv0 < (CAUSAL ? min(n, qw0 + 32) : n); kv0 += 32 * KS) {
       f32x16 s[1] = {zero16()};
       rows_f32<D>(s[0], Kg, kv0 + perm32(c), Qg, qi, n, a.qflip, h);
-      softmax(kv0, s);
+      softmax(kv0, s, 1.f);
       cols_f32<D>(oacc, Vg, kv0, n, s[0], h, c);
     }
   }
@@ -426,7 +450,8 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
   const float* Qg = (const float*)a.q + hoff;
   const float* dOg = (const float*)a.dout + hoff;
   RowParts<D> q, g;
-  const bool own_q = q.load(Qg, qi, n, h, a.qflip), own_g = g.load(dOg, qi, n, h, 0u), own = own_q || own_g;
+  // dO and D 2^24 times as large, so that dS is
+  const bool own_q = q.load(Qg, qi, n, h, a.qflip), own_g = g.load(dOg, qi, n, h, 0u, kUp), own = own_q || own_g;
   const float lq = qi < n ? a.lse2[(size_t)head * n + qi] : 0.f;
   const float nd = qi < n ? a.dvec[(size_t)head * n + qi] : 0.f;   // -D
 
@@ -435,7 +460,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
   for (int db = 0; db < NDB; ++db) dqa[db] = zero16();
   const float sl2 = a.sl2;
   // dS of the 32 keys from kv0 on, from S and dP (which becomes dS)
-  auto grad = [&](int kv0, const f32x16& s, f32x16& dp) __attribute__((always_inline)) {
+  auto grad = [&](int kv0, const f32x16& s, f32x16& dp, float nd) __attribute__((always_inline)) {
     const bool edge = kv0 + 32 > n || (CAUSAL && kv0 + 31 > qw0);
     const int lim = (CAUSAL ? min(qi, n - 1) : n - 1) - (kv0 + 16 * h);
 #pragma unroll
@@ -468,7 +493,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
         mma6(s, row_parts<D, BT>(kl, rb, t, h, c), q.f[t]);
         mma6(dp, row_parts<D, BT>(vl, rb, t, h, c), g.f[t]);
       }
-      grad(kv0, s, dp);
+      grad(kv0, s, dp, nd * kUp);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const Parts f = split3(dp, t);
@@ -478,7 +503,12 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
     }
   }
 
+  __builtin_amdgcn_sched_barrier(0);   // keeps the test out of the loop's schedule (35 more spills without)
   if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(dqa));
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) dqa[db][j] *= kDown;
   if (slow) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) dqa[db] = zero16();
@@ -487,7 +517,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
       f32x16 s = zero16(), dp = zero16();
       rows_f32<D>(s, Kg, kv0 + perm32(c), Qg, qi, n, a.qflip, h);
       rows_f32<D>(dp, Vg, kv0 + perm32(c), dOg, qi, n, 0u, h);
-      grad(kv0, s, dp);
+      grad(kv0, s, dp, nd);
       cols_f32<D>(dqa, Kg, kv0, n, dp, h, c);
     }
   }
@@ -568,9 +598,9 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
 #pragma unroll
   for (int db = 0; db < NDB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
   const float sl2 = a.sl2;
-  // P (in s) and dS (in dp) of the tile's 32 queries from qb0 on, from S and
+  // up P (in s) and up dS (in dp) of the tile's 32 queries from qb0 on, from S and
   // dP; lane (h, c): element j is query qb0 + 16h + j, key kj
-  auto grad = [&](int rb, int qb0, f32x16& s, f32x16& dp) __attribute__((always_inline)) {
+  auto grad = [&](int rb, int qb0, f32x16& s, f32x16& dp, float up) __attribute__((always_inline)) {
     const bool edge = qb0 + 32 > n || (CAUSAL && qb0 < kw0 + 31);
     const int qbase = qb0 + 16 * h, lo = CAUSAL ? kj - qbase : -1, hi = n - 1 - qbase;
 #pragma unroll
@@ -580,7 +610,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = 4 * j4 + e;
-        float p = exp2_fast(fmaf(s[j], sl2, -l4[e]));
+        float p = exp2_fast(fmaf(s[j], sl2, -l4[e])) * up;
         if (edge) p = (j < lo || j > hi) ? 0.f : p;
         s[j] = p;
         dp[j] = p * (dp[j] + d4[e]);   // d4 holds -D
@@ -608,7 +638,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
         mma6(s, row_parts<D, BT>(ql, rb, t, h, c), k.f[t]);
         mma6(dp, row_parts<D, BT>(ol, rb, t, h, c), v.f[t]);
       }
-      grad(rb, qb0, s, dp);
+      grad(rb, qb0, s, dp, kUp);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const Parts pf = split3(s, t);
@@ -621,7 +651,15 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
     }
   }
 
+  __builtin_amdgcn_sched_barrier(0);   // keeps the test out of the loop's schedule (35 more spills without)
   if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(dk) || any_nonfinite(dv));
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      dk[db][j] *= kDown;
+      dv[db][j] *= kDown;
+    }
   if (slow) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
@@ -634,7 +672,7 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
       f32x16 s = zero16(), dp = zero16();
       rows_f32<D>(s, Qg, qb0 + perm32(c), Kg, kj, n, a.qflip, h);
       rows_f32<D>(dp, dOg, qb0 + perm32(c), Vg, kj, n, 0u, h);
-      grad(0, qb0, s, dp);
+      grad(0, qb0, s, dp, 1.f);
       cols_f32<D>(dv, dOg, qb0, n, s, h, c);
       cols_f32<D>(dk, Qg, qb0, n, dp, h, c);
     }

@@ -90,6 +90,44 @@ def test_keys_masked_by_an_overflowing_product(d, causal, qcol, pad):
 
 @pytest.mark.parametrize("d", [32, 64, 128])
 @pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("which,shrink", [("do", 108), ("do", 116), ("do", 120), ("v", 116), ("q", 120), ("k", 120)])
+def test_small_operands_keep_their_bits(d, causal, which, shrink):
+    """One operand down by a power of two, to where its low part would fall under
+    the smallest bfloat16: results as precise as those of float32 products."""
+    n, heads = 200, 200
+    w = workloads.Workload("small", 1, heads, n, d, "f32", causal, 1.0, 1.0, 1.0, d + shrink)
+    inp = workloads.generate(w)
+    setattr(inp, which, getattr(inp, which) * np.float32(2.0 ** -shrink))
+    got = run_fwd_bwd(to_gpu(inp), w.scale, causal)
+    some = [(0, 0), (0, heads - 1)]
+    ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, causal, heads=some)
+    errs = compare({k: np.stack([to_host64(got[k])[b, h] for b, h in some]) for k in OUTPUTS}, ref)
+    # as test_tile_edges; dS of 2^-120 P is subnormal, to 2^-149: 2^-20 of the largest
+    assert all(v <= 1e-5 for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_small_probabilities_keep_their_bits(d):
+    """Keys 80 below the others, P about 2^-123: their rows of dK and dV, and a
+    column of O that only they reach, are as precise as the rest."""
+    n, heads, tail = 200, 200, 150
+    w = workloads.Workload("smallp", 1, heads, n, d, "f32", False, 0.1, 1.0, 1.0, d)
+    inp = workloads.generate(w)
+    inp.q[..., 0], inp.k[..., 0] = 1.0, 0.0
+    inp.k[..., tail:, 0] = -80.0
+    inp.v[..., :tail, 1] = 0.0
+    inp.v[..., tail:, 1] = np.abs(inp.v[..., tail:, 1])
+    got = run_fwd_bwd(to_gpu(inp), 1.0, False)
+    ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, 1.0, False, heads=[(0, heads - 1)])
+    cut = {"O": np.s_[:, 1], "dK": np.s_[tail:], "dV": np.s_[tail:]}
+    errs = {k: max_rel(to_host64(got[k])[0, heads - 1][x], np.asarray(ref[k])[0][x]) for k, x in cut.items()}
+    # each of the up to 64 additions that form a score of -80 rounds it to 2^-18 =
+    # 3.8e-6, which is as much of P: 3e-5 when they are independent
+    assert all(v <= 1e-4 for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("lse,do,v", [(0.0, 1.5e19, 3.4e38 / 1.5e19), (-60.0, 1.8e6, 3.4e38 / 1.8e6 / np.exp(60.0))])
 def test_dS_up_to_the_largest_float(d, causal, lse, do, v):
     """dS = 3.4e38, which bfloat16 rounds to infinity, gives the dQ that float32
