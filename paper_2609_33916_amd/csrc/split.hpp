@@ -17,7 +17,7 @@
 // transposed go through LDS tiles that belong to one wave (LDS DMA, two
 // stages), in float32 they are 4-byte loads, one row of 32 columns per lane
 // half, also straight into registers. Rows past the end repeat the last row
-// and are masked.
+// and are masked (the float32 transposed operands read zeros there).
 #pragma once
 
 #include "kernels.hpp"
@@ -91,20 +91,25 @@ template <int D> __device__ __forceinline__ void mma_rows(f32x16& acc, const Row
 
 // float32: columns of 32 rows as transposed operands (row 16h + t for k-step
 // t), loaded R k-steps ahead of their products (a k-step's products take
-// 64 D/32 cycles, so 8 steps, or 4 at d = 128, cover a load from L2).
+// 64 D/32 cycles, so 8 steps, or 4 at d = 128, cover a load from L2). Buffer
+// loads, whose range ends with the matrix: rows past the end read as zeros (the
+// other operand is zero there, and a repeated last row may hold an infinity).
 template <int D> struct ColRegs {
   static constexpr int NDB = D / 32, R = D == 128 ? 4 : 8;
   float v[R][NDB];
-  const float* g;
-  int row0, last, c;
+  __amdgpu_buffer_rsrc_t rs;
+  unsigned off;   // in bytes
+  // x: a [n, D] matrix (below 2 GB: small grids)
+  __device__ __forceinline__ ColRegs(const float* x, int n)
+      : rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), (short)0, n * D * 4, 0x00020000)) {}
   __device__ __forceinline__ void get(int t) {
-    const float* p = g + (size_t)min(row0 + t, last) * D + c;
 #pragma unroll
-    for (int db = 0; db < NDB; ++db) v[t % R][db] = p[32 * db];
+    for (int db = 0; db < NDB; ++db)
+      v[t % R][db] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 4 * (t * D + 32 * db), 0));
   }
   // the first R k-steps of rows [r0, r0 + 32)
-  __device__ __forceinline__ void load(const float* x, int r0, int n, int h, int c_) {
-    g = x, row0 = r0 + 16 * h, last = n - 1, c = c_;
+  __device__ __forceinline__ void load(int r0, int h, int c) {
+    off = 4u * (unsigned)((r0 + 16 * h) * D + c);
 #pragma unroll
     for (int t = 0; t < R; ++t) get(t);
   }
@@ -261,10 +266,10 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 1 : 2) fwd_s
     }
   } else {
     RowRegs<T, D> k;
-    ColRegs<D> v;
+    ColRegs<D> v(Vg, n);
     if (w < nb) {
       kload(w, k);
-      v.load(Vg, 32 * w, n, h, c);
+      v.load(32 * w, h, c);
     }
     if (qi < n) q.load((const T*)a.q + hoff + (size_t)qi * D, h, a.qflip);
     else q.zero();
@@ -274,7 +279,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 1 : 2) fwd_s
       if (kb + 4 < nb) kload(kb + 4, k);
       softmax(kb, s);
       mma_cols<D>(oacc, v, s);
-      if (kb + 4 < nb) v.load(Vg, 32 * (kb + 4), n, h, c);
+      if (kb + 4 < nb) v.load(32 * (kb + 4), h, c);
     }
   }
 
@@ -408,11 +413,11 @@ __device__ __forceinline__ void dq_split(const BwdArgs& a, int bid, float* stA, 
     }
   } else {
     RowRegs<T, D> k, v;
-    ColRegs<D> kc;
+    ColRegs<D> kc(Kg, n);
     if (w < nb) {
       rows(Kg, w, k);
       rows(Vg, w, v);
-      kc.load(Kg, 32 * w, n, h, c);
+      kc.load(32 * w, h, c);
     }
     own();
     for (int kb = w; kb < nb; kb += 4) {
@@ -424,7 +429,7 @@ __device__ __forceinline__ void dq_split(const BwdArgs& a, int bid, float* stA, 
       if (more) rows(Vg, kb + 4, v);
       grad(kb, s, dp);
       mma_cols<D>(dqa, kc, dp);
-      if (more) kc.load(Kg, 32 * (kb + 4), n, h, c);
+      if (more) kc.load(32 * (kb + 4), h, c);
     }
   }
 
@@ -581,7 +586,7 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int bid, float* stA
     }
   } else {
     RowRegs<T, D> q, g;
-    ColRegs<D> qc, gc;
+    ColRegs<D> qc(Qg, n), gc(dOg, n);
     auto rows = [&](const T* x, int qb, RowRegs<T, D>& r) __attribute__((always_inline)) {
       r.load(x + (size_t)min(32 * qb + perm32(c), n - 1) * D, h);
     };
@@ -589,8 +594,8 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int bid, float* stA
       rows(Qg, b0 + w, q);
       rows(dOg, b0 + w, g);
       ldrows(b0 + w, ldA);
-      gc.load(dOg, 32 * (b0 + w), n, h, c);
-      qc.load(Qg, 32 * (b0 + w), n, h, c);
+      gc.load(32 * (b0 + w), h, c);
+      qc.load(32 * (b0 + w), h, c);
     }
     own();
     auto step = [&](int qb, float (&lc)[4][2][64], float (&ln)[4][2][64]) __attribute__((always_inline)) {
@@ -608,9 +613,9 @@ __device__ __forceinline__ void dkdv_split(const BwdArgs& a, int bid, float* stA
       }
       grad(qb, lc, s, dp);
       mma_cols<D>(dv, gc, s);
-      if (more) gc.load(dOg, 32 * (qb + 4), n, h, c);
+      if (more) gc.load(32 * (qb + 4), h, c);
       mma_cols<D>(dk, qc, dp);
-      if (more) qc.load(Qg, 32 * (qb + 4), n, h, c);
+      if (more) qc.load(32 * (qb + 4), h, c);
       __builtin_amdgcn_s_waitcnt(0xC07F);
     };
     for (int qb = b0 + w; qb < nb; qb += 8) {

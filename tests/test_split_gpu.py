@@ -62,3 +62,26 @@ def test_one_launch_equals_two(dtype, d, causal, heads):
         ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, causal, heads=some)
         errs = compare({k: np.stack([to_host64(got[k])[b, x] for b, x in some]) for k in OUTPUTS}, ref)
         assert all(v <= TOL[dtype] for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("n", [33, 40, 97, 127, 128])
+def test_an_infinity_in_the_last_row_stays_one(d, causal, n):
+    """float32 tiles read zeros past the end: an infinity in the last row of V, or
+    of dO, makes its column of O, or of dV, infinite and no other value NaN."""
+    import torch
+    import paper_2609_33916_amd as lib
+    torch.manual_seed(n + d)
+    q, k, v, g = (torch.randn(1, 2, n, d, device="cuda") for _ in range(4))
+    vi, gi = v.clone(), g.clone()
+    vi[:, :, n - 1, 5] = float("inf")
+    gi[:, :, n - 1, 7] = float("inf")
+    o, lse = lib.attn_fwd(q, k, vi, causal=causal)
+    _, _, _, _, dv = lib.attn_fwd_bwd(q, k, v, gi, causal=causal)
+    torch.cuda.synchronize()
+    seen = o[:, :, n - 1:] if causal else o   # the queries that see the last key
+    assert bool((seen[..., 5] == float("inf")).all()) and bool(torch.isfinite(lse).all())
+    assert bool((dv[..., 7] == float("inf")).all())
+    rest = torch.arange(d, device="cuda")
+    assert bool(torch.isfinite(o[..., rest != 5]).all()) and bool(torch.isfinite(dv[..., rest != 7]).all())
