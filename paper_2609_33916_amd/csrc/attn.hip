@@ -78,10 +78,7 @@ void launch_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
     hipLaunchKernelGGL((attn::fwd_pp_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(512), 0, st, a);
   } else {
     attn::set_grid(a, heads, kFwdBQ, fwd_per_cu<T>(D));
-    if (D == 64 && a.n <= 64)   // one tile per workgroup
-      hipLaunchKernelGGL((attn::fwd_kernel<D, CAUSAL, D != 64>), dim3(a.nblocks), dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((attn::fwd_kernel<D, CAUSAL, true>), dim3(a.nblocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attn::fwd_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
 

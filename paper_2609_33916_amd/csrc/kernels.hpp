@@ -128,21 +128,15 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(const PrepArgs a) {
 // BKV = 64 keys are staged in LDS (double-buffered through registers).
 // Per wave and key tile:  S^T = K Q^T (rows = keys, cols = the wave's 32
 // queries), online softmax per column, O^T += V^T P^T.
+// Every tile's maximum is formed (22 of some 160 VALU instructions). Forming it
+// only where an exponential came out at 2 or more, the tile then being done
+// again, was 1-6 % faster on scores of unit variance (128 heads, n = 4096, d = 32:
+// 407 / 382 us) but slower by 11 % at sigma 2 and by up to 58 % where the maximum
+// moves at every tile; with a wave doing so only while its maxima stay well
+// below the threshold, the second path's registers cost 1-6 % instead.
 // ======================================================================
-// P is held as 2^(S sl2 - m - kPShift), so that it reaches 2, and with it bit 14
-// of its bfloat16 pattern, when S sl2 exceeds m by kRescaleThresh: the OR of a
-// tile's operands says whether the maximum has to move, and the tile's own
-// maximum is only formed then (infinities and NaN have that bit too). VALU
-// issue bounds this kernel (75 % of its cycles, matrix cores 44 %), and the OR is
-// 8 instructions where the maximum is 22. 128 heads, n = 4096, forward before /
-// after: d = 32 407 / 382 us, causal 215 / 203; d = 64 606 / 598, causal 325 /
-// 321; n = 1537, 48 heads, d = 64 53.0 / 51.1. LAZY = false forms every tile's
-// maximum: at d = 64 it needs 40 registers less (four waves per SIMD instead of
-// three), which one tile per workgroup gains more from (1000 heads, n = 64:
-// 12.4 against 14.0 us).
-constexpr float kPShift = kRescaleThresh - 1.f;
-template <int D, bool CAUSAL, bool LAZY>
-__global__ void __launch_bounds__(256, LAZY ? 2 : 4) fwd_kernel(const FwdArgs a) {
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdArgs a) {
   using T = bf16;
   using E = Elem<T>;
   using Frag = typename E::frag;
@@ -197,71 +191,51 @@ __global__ void __launch_bounds__(256, LAZY ? 2 : 4) fwd_kernel(const FwdArgs a)
       const T* kl = cur[0];
       const T* vl = cur[1];
       f32x16 s[NKB];
-      auto scores = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < NKB; ++b) {
-          s[b] = zero16();
+      for (int b = 0; b < NKB; ++b) {
+        s[b] = zero16();
 #pragma unroll
-          for (int t = 0; t < TD; ++t) mma(s[b], RowRead<T, D>::get(kl, b, t, h, c), qf.f[t]);
-        }
-        // lane (h, c): s[b][j] = raw score of key kv0 + 32b + 16h + j, query qi
-        const bool edge = (kv0 + BKV > n) || (CAUSAL && kv0 + BKV - 1 > qw0);
-        if (edge) {
-          // keys after `last` are masked; the lane's keys of block b are base_b + j
-          const int last = CAUSAL ? min(qi, n - 1) : n - 1;
-#pragma unroll
-          for (int b = 0; b < NKB; ++b) {
-            const int lim = last - (kv0 + 32 * b + 16 * h);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) s[b][j] = (j > lim) ? -INFINITY : s[b][j];
-          }
-        }
-      };
-      scores();
-      // P of the tile as operands, its sum, and the OR of its bit patterns
-      Frag pf[NKB][T32];
-      float rs;
-      auto exps = [&](float mb) __attribute__((always_inline)) -> uint32_t {
-        uint32_t bits = 0;
-        rs = 0.f;
-#pragma unroll
-        for (int b = 0; b < NKB; ++b) {
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            s[b][j] = exp2_fast(fmaf(s[b][j], sl2, mb));
-            rs += s[b][j];
-          }
-#pragma unroll
-          for (int t = 0; t < T32; ++t) {
-            pf[b][t] = FragFromAcc<T>::get(s[b], t);
-            const u32x4 u = __builtin_bit_cast(u32x4, pf[b][t]);
-            bits |= u[0] | u[1] | u[2] | u[3];
-          }
-        }
-        return bits;
-      };
-      // (the first tile always sets the maximum)
-      if (!LAZY || it == 0 || __builtin_amdgcn_ballot_w64((exps(-kPShift - m_use) & 0x40004000u) != 0)) {
-        if (LAZY && it > 0) scores();   // again, K being at hand: kept, they would cost registers
-        float mx = -INFINITY;
-#pragma unroll
-        for (int b = 0; b < NKB; ++b)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[b][j]);
-        mx = halves_max(mx);
-        const float mt = mx * sl2;
-        const bool resc = mt > m_use + kRescaleThresh;
-        if (__builtin_amdgcn_ballot_w64(resc)) {
-          const float alpha = resc ? exp2_fast(m_use - mt) : 1.f;
-          if (resc) m_use = mt;
-          lsum *= alpha;
-#pragma unroll
-          for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
-        }
-        exps(m_use == -INFINITY ? 0.f : -kPShift - m_use);
+        for (int t = 0; t < TD; ++t) mma(s[b], RowRead<T, D>::get(kl, b, t, h, c), qf.f[t]);
       }
+      // lane (h, c): s[b][j] = raw score of key kv0 + 32b + 16h + j, query qi
+      const bool edge = (kv0 + BKV > n) || (CAUSAL && kv0 + BKV - 1 > qw0);
+      if (edge) {
+        // keys after `last` are masked; the lane's keys of block b are base_b + j
+        const int last = CAUSAL ? min(qi, n - 1) : n - 1;
+#pragma unroll
+        for (int b = 0; b < NKB; ++b) {
+          const int lim = last - (kv0 + 32 * b + 16 * h);
+#pragma unroll
+          for (int j = 0; j < 16; ++j) s[b][j] = (j > lim) ? -INFINITY : s[b][j];
+        }
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int b = 0; b < NKB; ++b)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[b][j]);
+      mx = halves_max(mx);
+      const float mt = mx * sl2;
+      const bool resc = mt > m_use + kRescaleThresh;
+      if (__builtin_amdgcn_ballot_w64(resc)) {
+        const float alpha = resc ? exp2_fast(m_use - mt) : 1.f;
+        if (resc) m_use = mt;
+        lsum *= alpha;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
+      }
+      const float mb = (m_use == -INFINITY) ? 0.f : -m_use;
+      float rs = 0.f;
+#pragma unroll
+      for (int b = 0; b < NKB; ++b)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const float p = exp2_fast(fmaf(s[b][j], sl2, mb));
+          rs += p;
+          s[b][j] = p;
+        }
       lsum += rs;
       // the PV products at a raised wave priority (forward 1-3 % faster;
       // raising it for the score products and exponentials instead, as in
@@ -271,9 +245,10 @@ __global__ void __launch_bounds__(256, LAZY ? 2 : 4) fwd_kernel(const FwdArgs a)
       for (int b = 0; b < NKB; ++b)
 #pragma unroll
         for (int t = 0; t < T32; ++t) {
+          const Frag pf = FragFromAcc<T>::get(s[b], t);
 #pragma unroll
           for (int db = 0; db < NDB; ++db)
-            mma(oacc[db], TransRead<T, D>::get(vl, b, db, t, h, c), pf[b][t]);
+            mma(oacc[db], TransRead<T, D>::get(vl, b, db, t, h, c), pf);
         }
       __builtin_amdgcn_s_setprio(0);
     }
@@ -314,7 +289,7 @@ __global__ void __launch_bounds__(256, LAZY ? 2 : 4) fwd_kernel(const FwdArgs a)
   const float dsum = halves_sum(dpart);
   if (qi < n && h == 0) {
     const size_t row = (size_t)head * n + qi;
-    const float l2 = m_use + (kPShift + log2f(ltot));
+    const float l2 = m_use + log2f(ltot);
     a.lse[row] = l2 * kLn2;
     if (dOg) {
       a.dvec[row] = -dsum;   // stored negated (the backward starts dP - D from it)
