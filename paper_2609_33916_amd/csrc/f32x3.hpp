@@ -11,11 +11,11 @@
 //
 // Infinities do not split, nor do values below 2^-110 other than 0, and part
 // products of large values overflow on their own (Range). Every tile and a
-// wave's own rows are tested for such values, and the accumulators at the end
-// for infinities and NaN, which P or dS beyond the range leave there (attn_bwd
-// takes any L and O). A workgroup that meets either starts over on the float32
-// matrix instructions with operands straight from memory: results there are
-// those of float32 arithmetic.
+// wave's own rows are tested for such values, and a workgroup that meets one goes
+// on from that tile with float32 matrix instructions, on tiles stored as they are
+// in the LDS of the parts. Accumulators that hold an infinity or NaN after the
+// fast tiles, which P or dS beyond the range leave there (attn_bwd takes any L and
+// O), are formed again that way. Results are those of float32 arithmetic then.
 //
 // Measured (us, float32 matrix instructions / these; MI355X): 64 heads, n =
 // 2048, d = 64: forward 557 / 390, dK/dV 1190 / 706, dQ 891 / 520; d = 128:
@@ -86,32 +86,6 @@ struct Range {
     return __builtin_amdgcn_ballot_w64(mx >= kSplitMax || mn < 2u * kSplitMin - 1u) != 0;
   }
 };
-// The float32 products for inputs that do not split.
-// acc += A B^T over d: rows arow of A and brow of B (zeros from row n on), B's
-// signs flipped by `flip`.
-template <int D>
-__device__ __forceinline__ void rows_f32(f32x16& acc, const float* A, int arow, const float* B, int brow, int n,
-                                         uint32_t flip, int h) {
-#pragma unroll 1
-  for (int u = 0; u < D / 8; ++u) {
-    u32x4 a = {0u, 0u, 0u, 0u}, b = a;
-    if (arow < n) a = *(const u32x4*)(A + (size_t)arow * D + 8 * u + 4 * h);
-    if (brow < n) b = *(const u32x4*)(B + (size_t)brow * D + 8 * u + 4 * h) ^ (u32x4){flip, flip, flip, flip};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) mma(acc, __uint_as_float(a[e]), __uint_as_float(b[e]));
-  }
-}
-// acc += A^T b over the rows [row0, row0 + 32) of a [n, D] matrix
-template <int D>
-__device__ __forceinline__ void cols_f32(f32x16 (&acc)[D / 32], const float* g, int row0, int n, const f32x16& b, int h, int c) {
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    const int row = row0 + 16 * h + t;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) mma(acc[db], row < n ? g[(size_t)row * D + 32 * db + c] : 0.f, b[t]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
 __device__ __forceinline__ void mma6(f32x16& acc, const Parts& a, const Parts& b) {
   mma(acc, a.lo, b.hi);
   mma(acc, a.hi, b.lo);
@@ -192,7 +166,30 @@ template <int ROWS, int D, int NT> struct Stage3 {
     }
     return m.left();
   }
+  // the tile as it is, in the layout of RowRead<float> and TransRead<float>
+  __device__ __forceinline__ void store_f32(float* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const int ci = tid + NT * i;
+      float* o = lds + srow(ci / C) * Tile<float, ROWS, D>::LD + 8 * (ci % C);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = __uint_as_float(r[i][e / 4][e % 4]);
+    }
+  }
 };
+// The float32 products, on tiles stored as they are (Stage3::store_f32).
+template <int D>
+__device__ __forceinline__ void rows_f32(f32x16& acc, const float* tile, int rb, const RowFrags<float, D>& b, int h, int c) {
+#pragma unroll
+  for (int t = 0; t < D / 2; ++t) mma(acc, RowRead<float, D>::get(tile, rb, t, h, c), b.f[t]);
+}
+template <int D, int ROWS>
+__device__ __forceinline__ void cols_f32(f32x16 (&acc)[D / 32], const float* tile, int rb, const f32x16& b, int h, int c) {
+#pragma unroll
+  for (int t = 0; t < 16; ++t)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) mma(acc[db], TransRead<float, D, ROWS>::get(tile, rb, db, t, h, c), b[t]);
+}
 // whether any of the NW waves set its flag
 template <int NW> __device__ __forceinline__ bool any_flag(const int (&f)[NW]) {
   int r = 0;
@@ -235,6 +232,8 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
   using ST = Stage3<BT, D, NT>;
   constexpr int MERGE = KS == 2 ? 4 * 64 * (16 * NDB + 2) * 4 : 0;   // bytes
   constexpr int TILES = 2 * 3 * ST::ELEMS * 2;
+  using TF = Tile<float, BT, D>;
+  static_assert(2 * TF::ELEMS * 4 <= TILES, "the float32 tiles go where the parts went");
   __shared__ __attribute__((aligned(16))) bf16 st[(TILES > MERGE ? TILES : MERGE) / 2];
   __shared__ int flag[4 * KS];   // per wave: its part of the tile does not split
   __shared__ int bad[4 * KS];    // per wave: its accumulators are not finite
@@ -304,8 +303,9 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
     lsum += rs;
   };
 
-  bool slow = false;
-  for (int it = 0; it < nt; ++it) {
+  bool slow = false;   // from tile `it` on
+  int it = 0;
+  for (; it < nt; ++it) {
     const int t0 = it * BT, kv0 = t0 + 32 * NB * ks;   // this group's first key
     __syncthreads();
     const bool huge_k = ksg.store(kl, tid), huge_v = vsg.store(vl, tid);
@@ -336,22 +336,45 @@ __global__ void __launch_bounds__(256 * KS, 2) fwd_x3_kernel(const FwdArgs a) {
   }
 
   __builtin_amdgcn_sched_barrier(0);   // keeps the test out of the loop's schedule (35 more spills without)
-  if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(oacc));
+  float down = kDown;
+  if (any_wave(bad, wv, lane, any_nonfinite(oacc))) {   // all over again
+    slow = true, it = 0, down = 0.f;
+    m_use = -INFINITY;
+    ksg.load(Kg, 0, n, tid);
+    vsg.load(Vg, 0, n, tid);
+  }
+  lsum = down == 0.f ? 0.f : lsum * down;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) oacc[db][j] *= kDown;
-  lsum *= kDown;
+    for (int j = 0; j < 16; ++j) oacc[db][j] = down == 0.f ? 0.f : oacc[db][j] * down;
   if (slow) {
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) oacc[db] = zero16();
-    m_use = -INFINITY, lsum = 0.f;
+    RowFrags<float, D> qf;
+    qf.load(Qg, qi, n, h, a.qflip);
+    float* const kf = (float*)st;
+    float* const vf = kf + TF::ELEMS;
 #pragma unroll 1
-    for (int kv0 = 32 * ks; kv0 < (CAUSAL ? min(n, qw0 + 32) : n); kv0 += 32 * KS) {
-      f32x16 s[1] = {zero16()};
-      rows_f32<D>(s[0], Kg, kv0 + perm32(c), Qg, qi, n, a.qflip, h);
+    for (; it < nt; ++it) {
+      const int t0 = it * BT;
+      __syncthreads();
+      ksg.store_f32(kf, tid);
+      vsg.store_f32(vf, tid);
+      __syncthreads();
+      if (it + 1 < nt) {
+        ksg.load(Kg, t0 + BT, n, tid);
+        vsg.load(Vg, t0 + BT, n, tid);
+      }
+      const int kv0 = t0 + 32 * NB * ks;
+      if (kv0 >= n || (CAUSAL && kv0 > qw0 + 31)) continue;
+      f32x16 s[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        s[b] = zero16();
+        rows_f32<D>(s[b], kf, NB * ks + b, qf, h, c);
+      }
       softmax(kv0, s, 1.f);
-      cols_f32<D>(oacc, Vg, kv0, n, s[0], h, c);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) cols_f32<D, BT>(oacc, vf, NB * ks + b, s[b], h, c);
     }
   }
 
@@ -427,6 +450,8 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
   using ST = Stage3<BT, D, NT>;
   constexpr int MERGE = KS == 2 ? 4 * 64 * 16 * NDB * 4 : 0;   // bytes
   constexpr int TILES = 2 * 3 * ST::ELEMS * 2;
+  using TF = Tile<float, BT, D>;
+  static_assert(2 * TF::ELEMS * 4 <= TILES, "the float32 tiles go where the parts went");
   __shared__ __attribute__((aligned(16))) bf16 st[(TILES > MERGE ? TILES : MERGE) / 2];
   __shared__ int flag[4 * KS];   // per wave: its part of the tile does not split
   __shared__ int bad[4 * KS];    // per wave: its accumulators are not finite
@@ -471,8 +496,9 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
     }
   };
 
-  bool slow = false;
-  for (int it = 0; it < nt; ++it) {
+  bool slow = false;   // from tile `it` on
+  int it = 0;
+  for (; it < nt; ++it) {
     const int t0 = it * BT;
     __syncthreads();
     const bool huge_k = ksg.store(kl, tid), huge_v = vsg.store(vl, tid);
@@ -504,21 +530,43 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dq_x3_kernel(const
   }
 
   __builtin_amdgcn_sched_barrier(0);   // keeps the test out of the loop's schedule (35 more spills without)
-  if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(dqa));
+  float down = kDown;
+  if (any_wave(bad, wv, lane, any_nonfinite(dqa))) {   // all over again
+    slow = true, it = 0, down = 0.f;
+    ksg.load(Kg, 0, n, tid);
+    vsg.load(Vg, 0, n, tid);
+  }
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) dqa[db][j] *= kDown;
+    for (int j = 0; j < 16; ++j) dqa[db][j] = down == 0.f ? 0.f : dqa[db][j] * down;
   if (slow) {
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) dqa[db] = zero16();
+    RowFrags<float, D> qf, gf;
+    qf.load(Qg, qi, n, h, a.qflip);
+    gf.load(dOg, qi, n, h, 0u);
+    float* const kf = (float*)st;
+    float* const vf = kf + TF::ELEMS;
 #pragma unroll 1
-    for (int kv0 = 32 * ks; kv0 < (CAUSAL ? min(n, qw0 + 32) : n); kv0 += 32 * KS) {
-      f32x16 s = zero16(), dp = zero16();
-      rows_f32<D>(s, Kg, kv0 + perm32(c), Qg, qi, n, a.qflip, h);
-      rows_f32<D>(dp, Vg, kv0 + perm32(c), dOg, qi, n, 0u, h);
-      grad(kv0, s, dp, nd);
-      cols_f32<D>(dqa, Kg, kv0, n, dp, h, c);
+    for (; it < nt; ++it) {
+      const int t0 = it * BT;
+      __syncthreads();
+      ksg.store_f32(kf, tid);
+      vsg.store_f32(vf, tid);
+      __syncthreads();
+      if (it + 1 < nt) {
+        ksg.load(Kg, t0 + BT, n, tid);
+        vsg.load(Vg, t0 + BT, n, tid);
+      }
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int rb = NB * ks + b, kv0 = t0 + 32 * rb;
+        if (kv0 >= n || (CAUSAL && kv0 > qw0 + 31)) continue;
+        f32x16 s = zero16(), dp = zero16();
+        rows_f32<D>(s, kf, rb, qf, h, c);
+        rows_f32<D>(dp, vf, rb, gf, h, c);
+        grad(kv0, s, dp, nd);
+        cols_f32<D, BT>(dqa, kf, rb, dp, h, c);
+      }
     }
   }
 
@@ -560,6 +608,8 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
   using ST = Stage3<BT, D, NT>;
   constexpr int MERGE = KS == 2 ? 4 * 64 * 16 * NDB * 4 : 0;   // bytes
   constexpr int TILES = 2 * 3 * ST::ELEMS * 2;
+  using TF = Tile<float, BT, D>;
+  static_assert(2 * TF::ELEMS * 4 <= TILES, "the float32 tiles go where the parts went");
   __shared__ __attribute__((aligned(16))) bf16 st[(TILES > MERGE ? TILES : MERGE) / 2];
   __shared__ int flag[4 * KS];   // per wave: its part of the tile does not split
   __shared__ int bad[4 * KS];    // per wave: its accumulators are not finite
@@ -618,8 +668,9 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
     }
   };
 
-  bool slow = false;
-  for (int it = 0; it < nt; ++it) {
+  bool slow = false;   // from tile `it` on
+  int it = 0;
+  for (; it < nt; ++it) {
     const int t0 = q_begin + it * BT;
     __syncthreads();
     const bool huge_q = qsg.store(ql, tid), huge_o = osg.store(ol, tid);
@@ -652,29 +703,44 @@ __global__ void __launch_bounds__(256 * KS, D == 128 ? 1 : 2) dkdv_x3_kernel(con
   }
 
   __builtin_amdgcn_sched_barrier(0);   // keeps the test out of the loop's schedule (35 more spills without)
-  if (!slow) slow = any_wave(bad, wv, lane, any_nonfinite(dk) || any_nonfinite(dv));
+  float down = kDown;
+  if (any_wave(bad, wv, lane, any_nonfinite(dk) || any_nonfinite(dv))) {   // all over again
+    slow = true, it = 0, down = 0.f;
+    load(q_begin);
+  }
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      dk[db][j] *= kDown;
-      dv[db][j] *= kDown;
+      dk[db][j] = down == 0.f ? 0.f : dk[db][j] * down;
+      dv[db][j] = down == 0.f ? 0.f : dv[db][j] * down;
     }
   if (slow) {
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
+    RowFrags<float, D> kf, vf;
+    kf.load(Kg, kj, n, h, a.qflip);
+    vf.load(Vg, kj, n, h, 0u);
+    float* const qt = (float*)st;
+    float* const ot = qt + TF::ELEMS;
 #pragma unroll 1
-    for (int qb0 = q_begin; qb0 < n; qb0 += 32) {   // block by block, through the first rows of ld
+    for (; it < nt; ++it) {
+      const int t0 = q_begin + it * BT;
       __syncthreads();
-      if (tid < 64) ld[tid >> 5][tid & 31] = (tid < 32 ? Lg : Dg)[min(qb0 + (tid & 31), n - 1)];
+      qsg.store_f32(qt, tid);
+      osg.store_f32(ot, tid);
+      if (tid < 2 * BT) (&ld[0][0])[tid] = lr;
       __syncthreads();
-      if (((qb0 >> 5) & (KS - 1)) != ks || (CAUSAL && qb0 + 31 < kw0)) continue;
-      f32x16 s = zero16(), dp = zero16();
-      rows_f32<D>(s, Qg, qb0 + perm32(c), Kg, kj, n, a.qflip, h);
-      rows_f32<D>(dp, dOg, qb0 + perm32(c), Vg, kj, n, 0u, h);
-      grad(0, qb0, s, dp, 1.f);
-      cols_f32<D>(dv, dOg, qb0, n, s, h, c);
-      cols_f32<D>(dk, Qg, qb0, n, dp, h, c);
+      if (it + 1 < nt) load(t0 + BT);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int rb = NB * ks + b, qb0 = t0 + 32 * rb;
+        if (qb0 >= n || (CAUSAL && qb0 + 31 < kw0)) continue;
+        f32x16 s = zero16(), dp = zero16();
+        rows_f32<D>(s, qt, rb, kf, h, c);
+        rows_f32<D>(dp, ot, rb, vf, h, c);
+        grad(rb, qb0, s, dp, 1.f);
+        cols_f32<D, BT>(dv, ot, rb, s, h, c);
+        cols_f32<D, BT>(dk, qt, rb, dp, h, c);
+      }
     }
   }
 

@@ -128,6 +128,30 @@ def test_small_probabilities_keep_their_bits(d):
 
 @pytest.mark.parametrize("d", [32, 64, 128])
 @pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("which", ["q", "k", "v", "do"])
+@pytest.mark.parametrize("row,heads", [(5, 100), (200, 60), (330, 100), (519, 60)])
+def test_from_one_large_value_on(d, causal, which, row, heads):
+    """A value of 2^25 in one row: the tiles from there on take the float32
+    instructions, those before stay as they are; every row against float64."""
+    n = 520
+    w = workloads.Workload("large", 1, heads, n, d, "f32", causal, 1.0, 1.0, 1.0, d + row)
+    inp = workloads.generate(w)
+    getattr(inp, which)[:, :, row, 3] = 2.0 ** 25
+    other = {"q": "k", "k": "q", "v": "do", "do": "v"}[which]   # keeps S and dP of order 1
+    getattr(inp, other)[..., 3] *= np.float32(2.0 ** -25)
+    got = run_fwd_bwd(to_gpu(inp), w.scale, causal)
+    some = [(0, 0), (0, heads - 1)]
+    ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, causal, heads=some)
+    host = {k: np.stack([to_host64(got[k])[b, h] for b, h in some]) for k in OUTPUTS}
+    rest = np.arange(d) != 3
+    for cols in (rest, ~rest):   # the large value's column apart from the others
+        errs = {k: max_rel(host[k][..., cols], np.asarray(ref[k])[..., cols]) for k in OUTPUTS if k != "L"}
+        assert all(v <= 1e-5 for v in errs.values()), errs
+    assert max_rel(host["L"], np.asarray(ref["L"])) <= 1e-5
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("lse,do,v", [(0.0, 1.5e19, 3.4e38 / 1.5e19), (-60.0, 1.8e6, 3.4e38 / 1.8e6 / np.exp(60.0))])
 def test_dS_up_to_the_largest_float(d, causal, lse, do, v):
     """dS = 3.4e38, which bfloat16 rounds to infinity, gives the dQ that float32
