@@ -161,11 +161,12 @@ int attn_fwd_bwd_timed(const void* Q, const void* K, const void* V, const void* 
  * The alternative Paper II weighs against recomputation (sections
  * sec:paper2-atomics, sec:paper2-gk-fix): instead of a separate dQ kernel
  * that recomputes S and dP per query block, the dK/dV kernel also forms
- * dQ = dS K for its block of 128 keys (32 keys on small grids) and adds it to
- * a float32 accumulator in the workspace with atomic adds, B*H*n*d per key
- * block without a mask (about half that under the causal mask); a last pass writes
- * dQ = scale * accumulator in bfloat16. Same results as attn_fwd_bwd within
- * rounding; dQ's summation order depends on scheduling, so repeated calls
+ * dQ = dS K for its block of 128 keys (32 keys on the smallest grids) and adds
+ * it to a float32 accumulator in the workspace with atomic adds, B*H*n*d per
+ * key block without a mask (about half that under the causal mask); a last pass
+ * writes dQ = scale * accumulator in bfloat16. Same results as attn_fwd_bwd
+ * within rounding (dK and dV of small grids may come from the other of the two
+ * dK/dV kernels); dQ's summation order depends on scheduling, so repeated calls
  * may differ in the last bits of dQ. bfloat16 only (ATTN_E_UNSUPPORTED for
  * float32). */
 

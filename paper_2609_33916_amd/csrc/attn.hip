@@ -126,7 +126,7 @@ void launch_dq(attn::BwdArgs a, int heads, hipStream_t st) {
 template <typename T, int D, bool CAUSAL>
 void launch_dkdv_aq(attn::BwdArgs a, int heads, hipStream_t st) {
   if constexpr (std::is_same<T, bf16>::value) {
-    if (attn::use_split(attn::kDkdv, true, D, CAUSAL, heads, a.n)) {   // as the fused path: the same dK and dV
+    if (attn::use_split_atomic(D, CAUSAL, heads, a.n)) {
       attn::launch_dkdv_split<T, D, CAUSAL, true>(a, heads, st);
       return;
     }

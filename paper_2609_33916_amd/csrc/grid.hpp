@@ -109,6 +109,22 @@ inline bool use_split(Kind kind, bool b16, int d, bool causal, int heads, int n)
   return (long long)heads * ((n + 127) / 128) <= split_limit(kind, b16, d, causal && n >= 512);
 }
 
+// The atomic-dQ form adds a float32 dQ per key block, four times as many from
+// 32-key blocks as from 128-key ones, so its dK/dV leaves the split kernel much
+// earlier (below the fused path's limits, so that dK and dV are the same bits
+// there). Whole call, split / large-grid kernel, in time of the large-grid
+// kernels throughout, n = 512 / 2048 / 8192: d = 32 48 tiles 0.94, 0.76 / 1.00, 0.82,
+// 64 tiles 0.95, 0.91, 0.92 / 1.01, 0.82, 0.80; d = 64 32 tiles 0.79, 0.71 / 0.87,
+// 0.83, 48 tiles 0.95, 0.94 / 0.87, 0.82, 256 tiles 2.5, 3.0, 3.1 / 1.00; d = 128 32
+// tiles 0.77, 0.82 / 0.78, 0.83, 48 tiles 0.98, 1.11 / 0.78, 0.83. Causal: d = 32 96
+// tiles 0.96, 0.81 / 1.02, 0.82, 128 tiles 1.01, 0.94, 0.92 / 0.97, 0.82, 0.79; d = 64
+// 64 tiles 0.86, 0.77, 0.77 / 0.87, 0.82, 0.82, 80 tiles 0.97, 0.95 / 0.89, 0.85; d =
+// 128 48 tiles 0.72, 0.73 / 0.79, 0.82, 64 tiles 0.82, 0.85, 0.89 / 0.79, 0.82, 0.84.
+inline bool use_split_atomic(int d, bool causal, int heads, int n) {
+  constexpr int limit[3][2] = {{48, 96}, {32, 64}, {32, 48}};   // [d = 32, 64, 128][causal]
+  return (long long)heads * ((n + 127) / 128) <= limit[d == 32 ? 0 : d == 64 ? 1 : 2][causal && n >= 512];
+}
+
 // The float32 kernels of f32x3.hpp come with four waves, or (d <= 64) with
 // eight that share every tile. Eight keep two waves on each SIMD while there
 // is one workgroup per compute unit; with more, two workgroups of four are

@@ -4,7 +4,7 @@ The dK/dV kernel also accumulates dQ = dS K with float32 atomic adds; its
 outputs must meet the same bound against the float64 oracle as the fused
 path (bfloat16: max|T - T_ref| / max|T_ref| <= 2e-2), and agree with
 attn_fwd_bwd: O and L bit for bit (same forward kernel), dK and dV bit for
-bit (same products in the same order), dQ within the bound.
+bit at the sizes below (same products in the same order), dQ within the bound.
 """
 import pytest
 
@@ -68,6 +68,28 @@ def test_atomic_workloads(name, heads):
     ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, w.causal, heads=heads)
     host = {k: np.stack([to_host64(got[k])[b, h] for (b, h) in heads]) for k in OUTPUTS}
     _check(compare(host, ref), f"atomic {name}")
+
+
+@pytest.mark.parametrize("d,causal,limit", [(32, False, 48), (32, True, 96), (64, False, 32), (64, True, 64),
+                                            (128, False, 32), (128, True, 48)])
+def test_atomic_both_sides_of_its_limit(d, causal, limit):
+    """The last grid (in 128-row tiles) of the 32-key blocks and the first of the
+    large kernel, with a last tile of 9 rows; below, dK and dV are those of
+    attn_fwd_bwd bit for bit."""
+    import numpy as np
+    import torch
+    n = 521   # five tiles a head
+    for heads in (limit // 5, limit // 5 + 1):
+        w = workloads.Workload("aq_limit", 1, heads, n, d, "bf16", causal, 1.0, 1.0, 0.1, d + heads)
+        inp = workloads.generate(w)
+        dev = to_gpu(inp)
+        got = _run(dev, w.scale, causal)
+        some = [(0, 0), (0, heads - 1)]
+        ref = oracle.attention(inp.q, inp.k, inp.v, inp.do, w.scale, causal, heads=some)
+        _check(compare({k: np.stack([to_host64(got[k])[b, h] for b, h in some]) for k in OUTPUTS}, ref), f"{w.name} {heads}")
+        if heads * 5 <= limit:
+            fused = run_fwd_bwd(dev, w.scale, causal)
+            assert all(torch.equal(fused[k], got[k]) for k in ("O", "L", "dK", "dV"))
 
 
 def test_atomic_rejects_float32():
