@@ -10,7 +10,7 @@ namespace attn {
 template <int D, bool CAUSAL> void launch_fwd_x3(FwdArgs a, int heads, hipStream_t st) {
   set_grid(a, heads, 128, 2);
   if constexpr (D != 128) {
-    if (x3_eight_waves(kFwd, D, CAUSAL, heads, a.n)) {
+    if (x3_eight_waves(D, CAUSAL, heads, a.n)) {
       hipLaunchKernelGGL((fwd_x3_kernel<D, CAUSAL, 2, D == 32 ? 128 : 64>), dim3(a.nblocks), dim3(512), 0, st, a);
       return;
     }
@@ -20,7 +20,7 @@ template <int D, bool CAUSAL> void launch_fwd_x3(FwdArgs a, int heads, hipStream
 template <int D, bool CAUSAL> void launch_dkdv_x3(BwdArgs a, int heads, hipStream_t st) {
   set_grid(a, heads, 128, D == 128 ? 1 : 2);
   if constexpr (D != 128) {
-    if (x3_eight_waves(kDkdv, D, CAUSAL, heads, a.n)) {
+    if (x3_eight_waves(D, CAUSAL, heads, a.n)) {
       hipLaunchKernelGGL((dkdv_x3_kernel<D, CAUSAL, 2, D == 32 ? 128 : 64>), dim3(a.nblocks), dim3(512), 0, st, a);
       return;
     }
@@ -30,7 +30,7 @@ template <int D, bool CAUSAL> void launch_dkdv_x3(BwdArgs a, int heads, hipStrea
 template <int D, bool CAUSAL> void launch_dq_x3(BwdArgs a, int heads, hipStream_t st) {
   set_grid(a, heads, 128, D == 128 ? 1 : 2);
   if constexpr (D != 128) {
-    if (x3_eight_waves(kDq, D, CAUSAL, heads, a.n)) {
+    if (x3_eight_waves(D, CAUSAL, heads, a.n)) {
       hipLaunchKernelGGL((dq_x3_kernel<D, CAUSAL, 2, D == 32 ? 128 : 64>), dim3(a.nblocks), dim3(512), 0, st, a);
       return;
     }

@@ -132,12 +132,11 @@ inline bool use_split_atomic(int d, bool causal, int heads, int n) {
 // / 2048, d = 64: 256 tiles forward 0.94 / 0.89, dK/dV 0.84 / 0.80, dQ 0.92 /
 // 0.88; 320 tiles 1.14 / 1.08, 1.13 / 1.10, 1.16 / 1.10; causal 384 tiles 1.01 /
 // 0.83, 0.84 / 0.72, 0.98 / 0.79, 512 tiles 1.09 / 0.89, 0.95 / 0.79, 1.07 /
-// 0.85. The d = 32 forward, whose tiles cost it more to split than to use, is
-// faster with eight at every size (64 heads, n = 2048: 211 against 216 us) but
-// those of n <= 64, which leave the second four nothing.
-inline bool x3_eight_waves(Kind kind, int d, bool causal, int heads, int n) {
+// 0.85; d = 32 forward 256 tiles 0.88 / 0.83, 288 tiles 1.11 / 1.05, at n = 128 1.01 and
+// 1.30 (1500 heads 1.50), causal 384 tiles 0.97 / 0.77, 416 tiles 1.09 / 0.77.
+// (n <= 64 leaves the second four nothing.)
+inline bool x3_eight_waves(int d, bool causal, int heads, int n) {
   if (d == 128 || n <= 64) return false;
-  if (d == 32 && kind == kFwd) return true;
   return (long long)heads * ((n + 127) / 128) <= (causal && n >= 512 ? 384 : 256);
 }
 
