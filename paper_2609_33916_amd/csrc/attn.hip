@@ -62,6 +62,17 @@ template <typename T> constexpr int fwd_per_cu(int d) {
   return std::is_same<T, bf16>::value ? (d == 128 ? 2 : 4) : (d == 128 ? 1 : d == 64 ? 2 : 3);
 }
 
+// Whether a causal forward takes the heads one by one: where a head is one tile,
+// so that there is nothing to order (1500 heads, n = 100, d = 64: 19.4 us in
+// groups, 18.6 so; 320 heads, d = 128: 19.8, 18.9), and, at d = 64, heads of a few
+// tiles in grids of more than two rounds, where a group's K and V outgrow L2 for
+// little imbalance (700 heads, n = 513: 66 and 60 us; 1500 heads, n = 200 39.5 and
+// 36.8, n = 300 60 and 55; but 320 heads, n = 1024 58 and 64, and at d = 128, 160
+// heads, n = 1024 75 and 95).
+bool one_by_one(const attn::FwdArgs& a, int per_cu, bool d64) {
+  return a.ntiles == 1 || (d64 && a.ntiles <= 6 && a.nblocks > 2 * attn::kXcds * attn::kCusPerXcd * per_cu);
+}
+
 // Small grids take the kernels of split.hpp. Otherwise, bf16 at d = 128: the
 // ping-pong forward (256 queries per eight-wave workgroup), and at d <= 64,
 // where a tile's softmax arithmetic outlasts its products, so that the
@@ -75,9 +86,11 @@ void launch_fwd(attn::FwdArgs a, int heads, hipStream_t st) {
     attn::launch_fwd_x3<D, CAUSAL>(a, heads, st);
   } else if constexpr (D == 128) {
     attn::set_grid(a, heads, kFwdPpBQ, 1);
+    if (one_by_one(a, 1, false)) a.hgroup = 0;
     hipLaunchKernelGGL((attn::fwd_pp_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(512), 0, st, a);
   } else {
     attn::set_grid(a, heads, kFwdBQ, fwd_per_cu<T>(D));
+    if (one_by_one(a, fwd_per_cu<T>(D), D == 64)) a.hgroup = 0;
     hipLaunchKernelGGL((attn::fwd_kernel<D, CAUSAL>), dim3(a.nblocks), dim3(256), 0, st, a);
   }
 }
