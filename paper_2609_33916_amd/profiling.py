@@ -67,13 +67,13 @@ def _last_template_arg_true(kernel: str) -> bool:
 def short_name(kernel: str) -> str:
     """Kernel name without template arguments; the backward kernels of the
     materialising path (template argument MAT = true) get a mat_ prefix, the
-    dK/dV kernel of the atomic-dQ form (AQ = true) an atomic_dq_ prefix.
-    dkdv16_kernel<D, CAUSAL, NW, BQ, MAT, AQ, KB>; dkdv_kernel and dq_kernel
-    end in MAT."""
+    dK/dV kernels of the atomic-dQ form (AQ = true) an atomic_dq_ prefix.
+    dkdv16_kernel<D, CAUSAL, NW, BQ, MAT, AQ, KB>; dkdv_split_kernel ends in AQ,
+    dq_kernel in MAT, as does the dkdv_kernel of traces of earlier builds."""
     k = kernel.replace("void ", "")
     for key in ("decode_append_kernel", "decode_combine_kernel", "decode_kernel",
                 "mat_fwd_kernel", "bwd_prep_kernel", "zero_f32_kernel", "dq_finalize_kernel", "fwd_pp_kernel",
-                "fwd_kernel", "fwd_split_kernel", "dkdv_split_kernel", "dq_split_kernel",
+                "fwd_kernel", "fwd_split_kernel", "bwd_split_kernel", "dkdv_split_kernel", "dq_split_kernel",
                 "fwd_x3_kernel", "dkdv_x3_kernel", "dq_x3_kernel",
                 "dkdv16_kernel", "mat_dkdv_kernel", "dkdv_kernel", "dq_kernel", "copyBuffer", "elementwise"):
         if key in k:
@@ -84,6 +84,10 @@ def short_name(kernel: str) -> str:
                 if len(args) >= 5 and args[4] == "true":
                     return "mat_" + key
                 return key
+            if key == "dkdv_split_kernel" and _last_template_arg_true(k):
+                return "atomic_dq_" + key
+            if key == "dkdv_split_kernel" and _last_template_arg_true(k):
+                return "atomic_dq_" + key
             if key in ("dkdv_kernel", "dq_kernel") and _last_template_arg_true(k):
                 return "mat_" + key
             return key
