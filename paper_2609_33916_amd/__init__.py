@@ -18,8 +18,10 @@ the call raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import math
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch  # loads the process's HIP runtime before the library
@@ -106,10 +108,15 @@ _native_lib = None   # ... this loaded library
 
 
 def _bind_native(L: ctypes.CDLL) -> None:
+    """Bind the module to the library. Without a built one every call takes the
+    Python form; one that does not load (built against another torch) is reported."""
     global _native, _native_lib
     try:
-        from . import _binding
-    except ImportError:
+        _binding = importlib.import_module(__name__ + "._binding")
+    except ModuleNotFoundError:
+        return
+    except ImportError as e:
+        warnings.warn(f"the native binding does not load, calls take the slower Python form: {e}", RuntimeWarning)
         return
     addr = [ctypes.cast(getattr(L, f), ctypes.c_void_p).value
             for f in ("attn_workspace_bytes", "attn_decode_workspace_bytes", "attn_fwd", "attn_fwd_bwd", "attn_bwd",

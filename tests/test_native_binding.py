@@ -1,6 +1,8 @@
 """The native form of the entry points (csrc/binding.cpp): it declines whatever
 is not plain, and where it answers, outputs, identities and errors are those of
 the Python form."""
+import warnings
+
 import pytest
 import torch
 
@@ -11,8 +13,8 @@ from helpers import gpu_available
 @pytest.fixture
 def native():
     pkg.lib()
-    if pkg._native is None:
-        pytest.skip("native binding not built")
+    # the package's build makes both: without the binding calls still work, slower
+    assert pkg._native is not None, "the library is built but its native binding is missing or does not load"
     return pkg._native
 
 
@@ -85,3 +87,22 @@ def test_given_outputs_workspace_stream_and_errors(native, monkeypatch):
                     bad()
                 seen.append((e.type, str(e.value)))
         assert seen[0] == seen[1]
+
+
+def test_a_binding_that_does_not_load_is_reported(monkeypatch):
+    """A missing module is no error; one that fails to import warns, and calls
+    go through the Python form in both cases."""
+    import importlib
+    loaded = pkg.lib()
+    for error in (ModuleNotFoundError("no module"), ImportError("undefined symbol: _ZN3c10")):
+        def fail(name):
+            raise error
+        with monkeypatch.context() as m, warnings.catch_warnings(record=True) as seen:
+            warnings.simplefilter("always")
+            m.setattr(pkg, "_native", None)
+            m.setattr(pkg, "_native_lib", None)
+            m.setattr(importlib, "import_module", fail)
+            pkg._bind_native(loaded)
+            assert pkg._native is None and pkg._native_lib is None
+        assert [str(w.message) for w in seen if "undefined symbol" in str(w.message)] == \
+            ([] if isinstance(error, ModuleNotFoundError) else [str(seen[-1].message)])
