@@ -106,3 +106,19 @@ def test_a_binding_that_does_not_load_is_reported(monkeypatch):
             assert pkg._native is None and pkg._native_lib is None
         assert [str(w.message) for w in seen if "undefined symbol" in str(w.message)] == \
             ([] if isinstance(error, ModuleNotFoundError) else [str(seen[-1].message)])
+
+
+def test_a_failed_binding_build_leaves_the_library(monkeypatch, tmp_path):
+    """The binding's compile may fail (no torch headers): the library is built,
+    the failure is told, and no stale binding stays behind."""
+    from paper_2609_33916_amd import build
+    lib_path, binding = tmp_path / "libattn_mi355x.so", tmp_path / "_binding.so"
+    binding.write_text("stale")
+    monkeypatch.setattr(build, "LIB_PATH", str(lib_path))
+    monkeypatch.setattr(build, "BINDING_PATH", str(binding))
+    monkeypatch.setattr(build, "SOURCES", {"empty.hip": []})
+    (tmp_path / "empty.hip").write_text("extern \"C\" int answer() { return 42; }\n")
+    monkeypatch.setattr(build, "binding_command", lambda out: ["false"])
+    with pytest.warns(RuntimeWarning, match="binding"):
+        assert build.build(out=str(lib_path), csrc=str(tmp_path)) == str(lib_path)
+    assert lib_path.exists() and not binding.exists()
