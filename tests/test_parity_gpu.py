@@ -80,9 +80,8 @@ def test_ragged_lengths(dtype, d, causal):
 @pytest.mark.parametrize("scale", [-0.3, 0.0, 1.7])
 @pytest.mark.parametrize("d,causal", [(64, True), (128, True), (128, False)])
 def test_scale_values(dtype, scale, d, causal):
-    """Negative, zero and large scales (zero gives uniform attention); at
-    d = 128 the bf16 dK/dV kernel takes a negative scale as the sign of
-    s log2(e) instead of a sign flip of K."""
+    """Negative, zero and large scales (zero gives uniform attention) on a small
+    grid, whose kernels flip the sign of Q or K for a negative scale."""
     w = workloads.Workload(f"scale_{dtype}_d{d}", 1, 2, 200, d, dtype, causal, 1.0, 1.0, 1.0, 77 + d)
     inp = workloads.generate(w)
     errs, _ = _full_compare(w, inp, causal, scale=scale)
@@ -93,9 +92,8 @@ def test_scale_values(dtype, scale, d, causal):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 def test_forward_entry_point(dtype, causal, d):
-    """attn_fwd alone (no dO: the forward writes no D); at d = 128 in bf16
-    this is the eight-wave forward, with 333 queries ending inside its
-    second 256-query workgroup."""
+    """attn_fwd alone (no dO: the forward writes no D) on a small grid, its 333
+    queries ending inside a workgroup's 32."""
     import torch
     import paper_2609_33916_amd as lib
     w = workloads.Workload(f"fwd_{dtype}_d{d}", 2, 3, 333, d, dtype, causal, 1.0, 1.0, 1.0, 55 + d)
