@@ -148,8 +148,10 @@ int attn_bwd(const void* Q, const void* K, const void* V, const void* O, const f
  * point to 4 hipEvent_t created by the caller; events[0] is recorded on
  * `stream` before the forward kernel, events[1] after it, events[2] after the
  * dK/dV kernel and events[3] after the dQ kernel, so hipEventElapsedTime of
- * consecutive pairs gives each kernel's device time. Same arguments, results
- * and errors as attn_fwd_bwd otherwise (a failed event record returns
+ * consecutive pairs gives each kernel's device time. (On small grids, where
+ * attn_fwd_bwd runs dK/dV and dQ in one launch, they are launched apart here,
+ * with the same results.) Same arguments, results and errors as attn_fwd_bwd
+ * otherwise (a failed event record returns
  * ATTN_E_HIP). */
 int attn_fwd_bwd_timed(const void* Q, const void* K, const void* V, const void* dO,
                        void* O, float* L, void* dQ, void* dK, void* dV,

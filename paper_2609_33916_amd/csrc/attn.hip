@@ -234,10 +234,13 @@ DecodePlan decode_plan(int B, int Hq, int Hkv, int n, int append) {
   long long ns = std::max<long long>(1, (kDecodeTargetWGs + groups - 1) / groups);
   ns = std::min(ns, tiles);
   // unsplit where the second pass (3 to 5 us) costs more than the longer chain:
-  // two tiles (1 sequence, 8 cache heads, n = 255: 9.1 us a step split, 8.2
-  // not; three tiles 9.2, 9.7), or a workgroup for every compute unit and up to
-  // 12 tiles (32 sequences, n = 767: 22.9 and 19.8; at n = 4096 with sequences
-  // of n/2 to n tokens 85 and 92, the splits even out their lengths)
+  // two tiles (1 sequence, 8 cache heads, n = 255, d = 64 / 128: 8.7 / 8.9 us a step
+  // split, 5.8 / 7.9 not; three tiles 9.0 / 9.4 and 6.9 / 9.4, four 9.0 / 9.3 and 7.8 /
+  // 10.9), or a workgroup for every compute unit and up to 12 tiles, beyond which
+  // splits pay where they even out lengths (32 sequences, 8 cache heads, time
+  // unsplit over split, d = 64 / 128, all of n tokens and of n / 2 to n: 6 tiles 0.86 /
+  // 0.85, 0.93 / 0.95; 12 tiles 0.95 / 0.88, 1.03 / 0.95; 16 tiles 0.98 / 0.94, 1.09 /
+  // 0.99; 24 tiles 1.02 / 0.96, 1.17 / 1.14)
   if (tiles <= 2 || (groups >= 256 && tiles <= 12)) ns = 1;
   const long long per = (tiles + ns - 1) / ns;     // most tiles of a split
   p.nsplit = (int)((tiles + per - 1) / per);

@@ -17,15 +17,24 @@
 // fast tiles, which P or dS beyond the range leave there (attn_bwd takes any L and
 // O), are formed again that way. Results are those of float32 arithmetic then.
 //
+// (The decomposition into bfloat16 parts is the one of Henry, Tang and Heinecke,
+// "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
+// Computations", 2019: three parts, six products.)
+//
 // Measured (us, float32 matrix instructions / these; MI355X): 64 heads, n =
-// 2048, d = 64: forward 557 / 390, dK/dV 1190 / 706, dQ 891 / 520; d = 128:
-// 1360 / 775, 2610 / 1485, 1795 / 1185; 32 heads, n = 1024, d = 64: 87 / 58,
-// 160 / 100, 121 / 75. Relative error against float64 over n = 128 to 8192 and
-// sigma 1 and 2: 0.5 to 1.0 of what it was (a product's 16 terms are added
-// before they are rounded, where the float32 instruction rounds every 2).
+// 2048, d = 64: forward 557 / 399, dK/dV 1189 / 715, dQ 892 / 523; d = 32: 289 / 245,
+// 558 / 421, 427 / 313; d = 128: 1349 / 789, 2613 / 1545, 1793 / 1189; 32 heads, n =
+// 1024, d = 64: 86 / 61, 159 / 103, 120 / 77. The tests for values that do not split,
+// the scaling of P and dS and the test of the accumulators are 2.5 % of that.
+// Relative error against float64 over n = 128 to 8192 and sigma 1 and 2: 0.5 to 1.0
+// of what it was (a product's 16 terms are added before they are rounded, where
+// the float32 instruction rounds every 2).
 // Bound by the matrix cores and the power they draw (1070 to 1200 TFLOP/s of
 // bfloat16 products, what a large bfloat16 matrix product reaches), then by
-// the VALU work of the splits.
+// the VALU work of the splits. With keys masked by -inf or by large values (64
+// heads, n = 2048, d = 64; a quarter of the keys, every eighth): forward 546 on the
+// float32 instructions throughout, 417 and 541 here; d = 128, 32 heads, n = 1024:
+// 175, 145 and 164; worst at d = 32 without a mask, every eighth key: 77 and 91.
 //
 // Tiles are read from memory as float32, a tile ahead, into registers, split
 // once, and written to LDS as three bfloat16 tiles in the layouts of RowRead

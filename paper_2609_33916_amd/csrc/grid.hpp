@@ -66,13 +66,28 @@ ATTN_HD int head_group(int heads, int ntiles, int per_cu) {
 // grids (split.hpp) take: up to there they are faster, their quarter-length
 // chains of steps outweighing that each key tile serves 32 queries instead of
 // 128 or 256. Under the causal mask that holds for about twice the tiles, half
-// of them being short. Time of the large-grid kernels over theirs, measured
-// at n = 512 / 2048 / 8192:
-//   bf16, d = 128, forward  64 tiles 2.05 / 2.07 / 2.01, 128 tiles 1.38 / 1.18 / 1.10, 192 tiles 1.06 / 0.87 / 0.78
-//   the same causal         64 tiles 2.15 / 2.13 / 2.18, 256 tiles 1.11 / 1.11 / 1.05, 384 tiles 0.87 / 0.84 / 0.77
-//   bf16, d = 64, dK/dV     64 tiles 2.12 / 2.92 / 3.38, 256 tiles 1.04 / 1.18 / 1.23, 512 tiles 0.83 / 0.81 / 0.81
-//   f32, d = 64, dQ         64 tiles 1.54 / 1.65 / 1.68,  96 tiles 0.80 / 0.78,        256 tiles 0.51 / 0.48 / 0.46
-//   the same causal         64 tiles 1.57 / 1.69 / 1.71, 128 tiles 0.99 / 0.98 / 1.00, 256 tiles 0.69 / 0.68 / 0.68
+// of them being short. Time of the large-grid kernels over theirs, at the
+// last grid within the limit and the first beyond it (tiles: n = 512 / 2048; the
+// float32 kernels of both sides have changed since, the split ones becoming up to
+// 25 % faster, so that some of their limits lie early):
+//   bf16 forward    d=32   192: 1.19 / 1.45, 208: 1.01 / 1.20 |  384: 1.02 / 1.35, 416: 0.95 / 1.36
+//   bf16 forward    d=64   128: 1.20 / 1.38, 144: 0.91 / 0.98 |  192: 1.09 / 1.40, 208: 0.99 / 1.33
+//   bf16 forward    d=128  128: 1.31 / 1.20, 144: 0.97 / 0.84 |  256: 1.00 / 1.07, 288: 0.93 / 0.98
+//   bf16 dK/dV      d=32   192: 1.07 / 1.21, 208: 0.91 / 1.01 |  320: 1.10 / 1.38, 352: 1.07 / 1.36
+//   bf16 dK/dV      d=64   256: 1.03 / 1.23, 288: 0.89 / 1.00 |  384: 1.08 / 1.49, 416: 0.97 / 1.32
+//   bf16 dK/dV      d=128  112: 0.99 / 1.17, 128: 0.98 / 1.17 |  160: 0.92 / 1.28, 176: 0.87 / 1.13
+//   bf16 dQ         d=32   384: 1.06 / 1.16, 416: 0.96 / 1.07 |  384: 1.25 / 1.63, 416: 1.18 / 1.58
+//   bf16 dQ         d=64   192: 0.96 / 1.07, 208: 0.81 / 0.86 |  224: 1.06 / 1.60, 256: 0.99 / 1.37
+//   bf16 dQ         d=128  128: 1.10 / 1.29, 144: 0.85 / 0.91 |  192: 0.94 / 1.30, 208: 0.88 / 1.21
+//   f32  forward    d=32   128: 1.38 / 1.46, 144: 1.01 / 1.02 |  176: 1.26 / 1.54, 192: 1.25 / 1.47
+//   f32  forward    d=64   80: 1.24 / 1.29, 96: 1.23 / 1.28 |  128: 1.54 / 1.69, 144: 1.32 / 1.46
+//   f32  forward    d=128  128: 1.35 / 1.43, 144: 0.96 / 1.04 |  256: 1.11 / 1.31, 288: 1.00 / 1.25
+//   f32  dK/dV      d=32   80: 1.17 / 1.22, 96: 1.16 / 1.21 |  176: 1.07 / 1.44, 192: 0.99 / 1.42
+//   f32  dK/dV      d=64   80: 1.06 / 1.06, 96: 1.05 / 1.06 |  192: 0.95 / 1.13, 208: 0.86 / 1.10
+//   f32  dK/dV      d=128  80: 1.05 / 1.07, 96: 1.05 / 1.08 |  160: 1.09 / 1.18, 176: 0.79 / 0.84
+//   f32  dQ         d=32   80: 1.15 / 1.17, 96: 1.15 / 1.16 |  144: 1.17 / 1.33, 160: 1.12 / 1.24
+//   f32  dQ         d=64   80: 1.02 / 0.98, 96: 1.01 / 0.98 |  112: 1.33 / 1.37, 128: 1.34 / 1.32
+//   f32  dQ         d=128  128: 1.12 / 1.23, 144: 0.77 / 0.83 |  208: 0.89 / 1.18, 224: 0.91 / 1.18
 // With n below 512 a causal head has too few short tiles for the causal limit
 // (250 heads, n = 100, bf16, d = 64: 0.91), and at n <= 128 a bf16 backward at
 // d = 128 has at most four steps to share (n = 33 to 100, dK/dV: 0.81-0.92).
@@ -89,13 +104,16 @@ constexpr int split_limit(Kind kind, bool b16, int d, bool causal) {
 }
 // The split kernels of the backward run in one launch (bwd_split_kernel) where
 // that is faster than two, and than the large-grid kernels: neither fills the
-// chip, so they run side by side, and a launch's fixed time is saved. Time of
-// two launches over one: 1.4-1.7 up to 32 tiles; bf16, d = 64, n = 512 / 2048 /
-// 8192: 64 tiles 1.32 / 1.29 / 1.31, 256 tiles 1.02 / 1.02 / 1.02, causal 256
-// tiles 1.12 / 1.29 / 1.42, 384 tiles 0.99 / 1.09; d = 128 (dK/dV takes a
-// compute unit's LDS) 96 tiles 1.24 / 1.25, 128 tiles 0.98 / 1.09 / 1.14, 192
-// tiles 0.73 / 0.83; float32, d = 64: 96 tiles 1.20 / 1.20, 128 tiles 0.95 /
-// 0.94 / 0.93.
+// chip, so they run side by side, and a launch's fixed time is saved (1.4-1.7 up
+// to 32 tiles). Time of the better of two split and two large-grid launches over
+// one, as above; bf16 at d = 128 and float32 at d >= 64 hold one workgroup per
+// compute unit (LDS, registers), which ends them at about half the others' limit:
+//   bf16 one launch d=32   320: 1.16 / 1.12, 352: 1.16 / 1.14 |  384: 1.17 / 1.07, 416: 1.17 / 1.03
+//   bf16 one launch d=64   256: 1.02 / 1.06, 288: 1.02 / 1.13 |  352: 1.07 / 1.04, 384: 1.02 / 1.01
+//   bf16 one launch d=128  112: 1.00 / 1.00, 128: 1.00 / 1.00 |  128: 1.05 / 1.10, 144: 1.10 / 1.08
+//   f32  one launch d=32   96: 1.10 / 1.08, 112: 1.06 / 1.01 |  192: 1.17 / 1.08, 208: 1.09 / 1.07
+//   f32  one launch d=64   96: 1.28 / 1.29, 112: 1.02 / 1.02 |  176: 1.06 / 1.04, 192: 0.99 / 1.06
+//   f32  one launch d=128  96: 1.26 / 1.25, 112: 1.01 / 1.01 |  112: 1.08 / 0.99, 128: 1.02 / 1.01
 inline bool one_backward(bool b16, int d, bool causal, int heads, int n) {
   constexpr int limit[2][3][2] = {   // [bf16][d = 32, 64, 128][causal]
       {{104, 192}, {104, 176}, {104, 112}}, {{320, 384}, {256, 352}, {112, 128}}};
@@ -112,8 +130,8 @@ inline bool use_split(Kind kind, bool b16, int d, bool causal, int heads, int n)
 // The atomic-dQ form adds a float32 dQ per key block, four times as many from
 // 32-key blocks as from 128-key ones, so its dK/dV leaves the split kernel much
 // earlier (below the fused path's limits, so that dK and dV are the same bits
-// there). Whole call, split / large-grid kernel, in time of the large-grid
-// kernels throughout, n = 512 / 2048 / 8192: d = 32 48 tiles 0.94, 0.76 / 1.00, 0.82,
+// there). Time of the whole call with the split / with the large-grid dK/dV, over
+// its time on large-grid kernels throughout, n = 512, 2048, 8192: d = 32 48 tiles 0.94, 0.76 / 1.00, 0.82,
 // 64 tiles 0.95, 0.91, 0.92 / 1.01, 0.82, 0.80; d = 64 32 tiles 0.79, 0.71 / 0.87,
 // 0.83, 48 tiles 0.95, 0.94 / 0.87, 0.82, 256 tiles 2.5, 3.0, 3.1 / 1.00; d = 128 32
 // tiles 0.77, 0.82 / 0.78, 0.83, 48 tiles 0.98, 1.11 / 0.78, 0.83. Causal: d = 32 96

@@ -1,8 +1,8 @@
 // Launchers that live in translation units of their own (the build script
 // gives each source its flags): bf16 dK/dV on 16x16x32 MFMA in dkdv.hip
-// (default machine scheduler), bf16 dQ in bwd.hip (iterative-ILP scheduler)
-// the kernels for small grids in split.hip and
-// the float32 kernels in f32x3.hip; the other kernels are launched from attn.hip, with the default scheduler.
+// (default machine scheduler), bf16 dQ in bwd.hip (iterative-ILP scheduler), the
+// kernels for small grids in split.hip and the float32 kernels in f32x3.hip; the
+// others are launched from attn.hip, with the default scheduler.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -48,7 +48,6 @@ template <typename T, int D, bool CAUSAL> void launch_fwd_split(FwdArgs a, int h
 template <typename T, int D, bool CAUSAL, bool AQ> void launch_dkdv_split(BwdArgs a, int heads, hipStream_t st);
 template <typename T, int D, bool CAUSAL> void launch_dq_split(BwdArgs a, int heads, hipStream_t st);
 template <typename T, int D, bool CAUSAL> void launch_bwd_split(BwdArgs a, int heads, hipStream_t st);   // both in one
-
 
 // The float32 kernels on the bfloat16 matrix cores (f32x3.hip).
 template <int D, bool CAUSAL> void launch_fwd_x3(FwdArgs a, int heads, hipStream_t st);

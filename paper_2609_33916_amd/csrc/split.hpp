@@ -9,8 +9,8 @@
 // launch's fixed 5 to 7 us), not by any unit's rate. Measured, large-grid
 // kernels / these (us): 16 heads, n = 1000, d = 128, causal, bf16: forward 37 /
 // 23, dK/dV 44 / 30, dQ 35 / 24; 1 head, n = 1024, d = 64, bf16: 20 / 11,
-// 34 / 13, 23 / 11; 8 heads, n = 1024, d = 64, float32: 84 / 30, 157 / 52,
-// 118 / 41. The limits are in grid.hpp.
+// 34 / 13, 23 / 11; 8 heads, n = 1024, d = 64, float32: 81 / 27, 153 / 47,
+// 116 / 38. The limits are in grid.hpp.
 //
 // Operands that are read as rows (contraction over d) go from global memory
 // straight into registers as the matrix operand; in bfloat16 the operands read
