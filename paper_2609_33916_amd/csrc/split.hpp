@@ -93,7 +93,8 @@ template <int D> __device__ __forceinline__ void mma_rows(f32x16& acc, const Row
 // t), loaded R k-steps ahead of their products (a k-step's products take
 // 64 D/32 cycles, so 8 steps, or 4 at d = 128, cover a load from L2). Buffer
 // loads, whose range ends with the matrix: rows past the end read as zeros (the
-// other operand is zero there, and a repeated last row may hold an infinity).
+// other operand is zero there, and a repeated last row may hold an infinity). The
+// whole offset is the vector one, which the range check covers.
 template <int D> struct ColRegs {
   static constexpr int NDB = D / 32, R = D == 128 ? 4 : 8;
   float v[R][NDB];
@@ -105,7 +106,7 @@ template <int D> struct ColRegs {
   __device__ __forceinline__ void get(int t) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
-      v[t % R][db] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 4 * (t * D + 32 * db), 0));
+      v[t % R][db] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off + 4u * (t * D + 32 * db), 0, 0));
   }
   // the first R k-steps of rows [r0, r0 + 32)
   __device__ __forceinline__ void load(int r0, int h, int c) {
