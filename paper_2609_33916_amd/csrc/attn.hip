@@ -221,7 +221,7 @@ void run_dispatch(int dtype, int d, int causal, Args a, int heads, hipStream_t s
 // until there are about two workgroups per compute unit, except in short
 // caches.
 struct DecodePlan {
-  int qchunks, nsplit;
+  int qchunks, nsplit, chunk;
 };
 constexpr int kDecodeTargetWGs = 512;
 DecodePlan decode_plan(int B, int Hq, int Hkv, int n, int append) {
@@ -244,6 +244,15 @@ DecodePlan decode_plan(int B, int Hq, int Hkv, int n, int append) {
   if (tiles <= 2 || (groups >= 256 && tiles <= 12)) ns = 1;
   const long long per = (tiles + ns - 1) / ns;     // most tiles of a split
   p.nsplit = (int)((tiles + per - 1) / per);
+  // A sequence's own tiles go evenly over the splits (of a fixed number each the
+  // last one got the remainder: 32 sequences of 2048 to 4096 tokens, two splits, d =
+  // 128, 88 us a step, 81 so; one of 4096 and 31 of 256: 53 and 41; 16 of 8191, 64
+  // heads, 105.7 and 99.4). With two long splits, where all workgroups run at once
+  // and only the time counts in which few are left, the fixed number is better: all
+  // first halves end together (32 sequences of 8192 to 16384, d = 64 / 128: 155 / 307
+  // us evenly, 149 / 304 so; of 4096 to 8191 83 / 152 and 79 / 151; of 3000 to 6000 56 /
+  // 122 and 56 / 121; but of 1500 to 3000 29 / 53 and 29 / 57).
+  p.chunk = p.nsplit == 2 && per >= 24 ? (int)per : 0;
   return p;
 }
 
@@ -675,7 +684,7 @@ int attn_decode(const void* q, const void* k_new, const void* v_new, void* k_cac
   a.o = O; a.lse = L;
   a.rows = B * Hq;
   a.Hq = Hq; a.Hkv = Hkv; a.G = Hq / Hkv; a.n = n; a.n_cap = n_cap; a.append = append;
-  a.nsplit = plan.nsplit; a.qchunks = plan.qchunks;
+  a.nsplit = plan.nsplit; a.qchunks = plan.qchunks; a.chunk = plan.chunk;
   a.sl2 = sp.sl2;
   a.qflip = sp.qflip;
   hipStream_t st = static_cast<hipStream_t>(stream);

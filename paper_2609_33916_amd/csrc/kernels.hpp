@@ -1559,6 +1559,7 @@ struct DecArgs {
   int Hq, Hkv, G, n, n_cap, append;
   int fuse_append;     // decode_kernel writes the new row itself (one query chunk per cache head)
   int nsplit, qchunks;
+  int chunk;           // tiles of a split, or 0: every sequence's own tiles evenly over the splits
   float sl2;
   uint32_t qflip;
 };
@@ -1606,11 +1607,11 @@ __global__ void __launch_bounds__(256) decode_kernel(const DecArgs a) {
   const int bh = grp / a.qchunks;                    // b * Hkv + hk
   const int b = bh / a.Hkv, hk = bh % a.Hkv;
   const int T_b = dec_len(a, b) + a.append;
-  // the sequence's own tiles, evenly over the splits (a fixed chunk per split
-  // left the last one the remainder: 32 sequences of 2048 to 4096 tokens, two
-  // splits, 80.6 us a step, 74.3 so; 16 of 8191, 64 heads, 105.7 and 99.4)
-  const unsigned tiles = (unsigned)(T_b + 127) / 128u, ns = (unsigned)a.nsplit;
-  const int k_lo = 128 * (int)(split * (size_t)tiles / ns), k_hi = min(T_b, 128 * (int)((split + 1) * (size_t)tiles / ns));
+  // the sequence's own tiles, evenly over the splits, or in chunks of a.chunk
+  const unsigned tiles = (unsigned)(T_b + 127) / 128u, ns = (unsigned)a.nsplit, ck = (unsigned)a.chunk;
+  const unsigned lo = ck ? min(split * ck, tiles) : (unsigned)(split * (size_t)tiles / ns);
+  const unsigned hi = ck ? min((split + 1) * ck, tiles) : (unsigned)((split + 1) * (size_t)tiles / ns);
+  const int k_lo = 128 * (int)lo, k_hi = min(T_b, 128 * (int)hi);
   const int h0 = hk * a.G + qc * 32;                 // first query head of this workgroup
   const int nq = min(32, a.G - qc * 32);             // query heads in it
   const size_t kvoff = (size_t)bh * a.n_cap * D;

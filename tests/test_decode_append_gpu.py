@@ -33,3 +33,30 @@ def test_stale_rows_are_not_read(d, Hq, Hkv, n):
     for b, x in enumerate(lens):
         assert torch.equal(kc[b, :, x], kn[b]) and torch.equal(vc[b, :, x], vn[b])
         assert torch.equal(kc[b, :, :x], k0[b, :, :x]) and bool(torch.isnan(kc[b, :, x + 1:]).all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [5887, 5888, 6015])
+def test_two_long_splits(d, n):
+    """Around the line (48 tiles of 128 keys) from which two splits take a fixed
+    number of tiles: sequences that end in the first split, at its end, in the
+    second and at n, the cache rows behind them NaN."""
+    import torch
+    import paper_2609_33916_amd as lib
+    B, Hq, Hkv = 64, 8, 4   # 256 workgroups: two splits
+    cut = 128 * ((n + 128) // 128 // 2)
+    lens = [1, 127, 128, cut - 129, cut - 1, cut, cut + 1, cut + 127, cut + 128, n - 128, n - 1] + [n] * (B - 11)
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    q, kn, vn = (torch.randn(B, h, d, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    kc, vc = (torch.randn(B, Hkv, n + 1, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    for b, x in enumerate(lens):
+        kc[b, :, x:] = float("nan")
+        vc[b, :, x:] = float("nan")
+    some = list(range(12))
+    k0, v0 = kc[some].clone(), vc[some].clone()
+    O, L = lib.attn_decode(q, kc, vc, kn, vn, cache_lens=torch.tensor(lens, dtype=torch.int32, device="cuda"), n=n)
+    torch.cuda.synchronize()
+    ref = dec.decode_step(*(to_host64(x) for x in (q[some], k0, v0)), np.array([lens[b] for b in some]), 1.0 / np.sqrt(d),
+                          to_host64(kn[some]), to_host64(vn[some]))
+    assert max_rel(to_host64(O[some]), ref["O"]) <= TOL["bf16"] and max_rel(to_host64(L[some]), ref["L"]) <= TOL["bf16"]
+    assert bool(torch.isfinite(O).all()) and bool(torch.isfinite(L).all())
