@@ -1,6 +1,7 @@
 """float32 on the bfloat16 matrix cores (GPU): four- and eight-wave workgroups
 on both sides of their limit, lengths at the tile edges, values that do not
-split (infinities, the type's largest), and the error against float64."""
+split (infinities, large ones and those below 2^-110, as operands, products,
+probabilities and dS), keys masked by value, and the error against float64."""
 import numpy as np
 import pytest
 
